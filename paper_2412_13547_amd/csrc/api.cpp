@@ -263,7 +263,15 @@ int ppt_of(const tgs_options& opt, int64_t tiles) {
                                  : tgs::default_pixels_per_thread(opt.tile, tiles);
 }
 
-// Depth sort and the pair counts per (tile row, chunk), up to the row starts
+// The two-level binning's device pair count (64 bits, in the depth sort's area).
+unsigned long long* pair_total(uint8_t* ws, const tgs::Layout& L) {
+    return reinterpret_cast<unsigned long long*>(ws + L.sort_counts + 4 * tgs::radix_spare_offset());
+}
+
+tgs_status launched(hipError_t e) { return e == hipSuccess ? TGS_OK : hip_fail(e, "kernel launch"); }
+
+// Depth sort and the pair counts: per supertile and in all, or (too many
+// supertiles) per (tile row, chunk), up to the row starts
 // and the device pair count.  Returns the depth-sort result buffer and the
 // device count of the Gaussians it holds.
 tgs_status enqueue_counts(uint8_t* ws, const tgs::Layout& L, const tgs::Grid& grid, int64_t n,
@@ -281,6 +289,8 @@ tgs_status enqueue_counts(uint8_t* ws, const tgs::Layout& L, const tgs::Grid& gr
     const uint32_t* kept = u32(L.sort_counts) + tgs::radix_kept_offset(uint64_t(n));
     *order = dvals[*dres];
     *dcount = kept;
+    if (L.super.supers)
+        return launched(tgs::launch_super_counts(ws, L, *order, n, kept, pair_total(ws, L), strm));
     // entries and pairs per (tile row, block of the depth order); scans ->
     // every block's place in every row
     const uint64_t nrow = uint64_t(grid.gy) * tgs::bin_blocks(n);
@@ -291,13 +301,17 @@ tgs_status enqueue_counts(uint8_t* ws, const tgs::Layout& L, const tgs::Grid& gr
     return TGS_OK;
 }
 
-// Entries into row buckets, then a stable counting sort by column per slice
+// The pairs and the ranges from the supertiles' lists; or, by rows, entries
+// into row buckets, then a stable counting sort by column per slice
 // of every row, which writes the pairs and the per-tile ranges.  `slices`
 // bounds the column-sort slices from above; the kernels skip all work when
 // the device pair count exceeds the capacity.
 tgs_status enqueue_emit(uint8_t* ws, const tgs::Layout& L, const tgs::Grid& grid, int64_t n,
                         const uint32_t* order, const uint32_t* dcount, uint64_t slices,
                         uint32_t capacity, hipStream_t strm) {
+    if (L.super.supers)
+        return launched(tgs::launch_super_lists(ws, L, order, n, dcount, pair_total(ws, L), grid,
+                                                capacity, strm));
     TGS_HIP(tgs::launch_entries(ws, L, order, n, dcount, grid, capacity, strm));
     TGS_HIP(tgs::launch_col_sort(ws, L, grid, slices, capacity, strm));
     return TGS_OK;
@@ -342,9 +356,12 @@ Layout make_layout(int64_t n, uint64_t cap, const Grid& grid) {
     L.srect = take(un * 8);
     for (int b = 0; b < 2; ++b) L.depth_key[b] = take(un * 4);
     for (int b = 0; b < 2; ++b) L.depth_val[b] = take(un * 4);
+    L.row_start = take((gy + 1) * 4);
+    L.pair_vals = take(cap * 4);
+    // the row binning's buffers; the two-level binning's lie over them where
+    // they fit, so a view's workspace has one size whichever bins it
     L.ecnt = take(table * 4);
     L.pcnt = take(table * 4);
-    L.row_start = take((gy + 1) * 4);
     L.erow = take((gy + 1) * 4);
     L.first_slice = take((gy + 1) * 4);
     L.slice_desc = take(slices * 16);
@@ -352,8 +369,9 @@ Layout make_layout(int64_t n, uint64_t cap, const Grid& grid) {
     L.ent_id = take(cap * 4);
     L.ent_pp = take(cap * 4);
     L.ent_x = take(cap * 4);
-    L.pair_vals = take(cap * 4);
     L.col_hist = take(hist * 4);
+    const uint64_t need = super_layout(L.super, L.ecnt, n, cap, grid);
+    if (need == 0 || need > o - L.ecnt) L.super.supers = 0;
     L.ranges = take(uint64_t(grid.num_tiles()) * 8);
     L.tile_work = take(uint64_t(grid.num_tiles()) * 4);
     L.tile_order = take(uint64_t(grid.num_tiles()) * 4);
@@ -433,6 +451,7 @@ tgs_status tgs_create(int device, tgs_context** out) {
         return fail(TGS_ERR_NO_DEVICE, "device %d not available (%d devices)", device, count);
     TGS_HIP(hipSetDevice(device));
     TGS_HIP(tgs::prepare_binning_kernels());
+    TGS_HIP(tgs::prepare_supertile_kernels());
     auto* ctx = new (std::nothrow) tgs_context{};
     if (!ctx) return fail(TGS_ERR_HIP, "out of host memory");
     ctx->device = device;
@@ -551,11 +570,13 @@ tgs_status tgs_bin_sort(tgs_context* ctx, const tgs_gaussians* g, const tgs_came
         // row starts (and the pair count) back to the host: a capacity
         // error can be reported now, and the column sort is launched with
         // exactly as many slices as there are
-        TGS_HIP(hipMemcpyAsync(ctx->pinned, ws + L.row_start, (uint64_t(grid.gy) + 1) * 4,
+        const bool super = L.super.supers != 0;
+        const void* src = super ? static_cast<const void*>(pair_total(ws, L)) : ws + L.row_start;
+        TGS_HIP(hipMemcpyAsync(ctx->pinned, src, super ? 8 : (uint64_t(grid.gy) + 1) * 4,
                                hipMemcpyDeviceToHost, strm));
         TGS_HIP(hipStreamSynchronize(strm));
         const uint32_t* rs = reinterpret_cast<const uint32_t*>(ctx->pinned);
-        const uint64_t P = rs[grid.gy];
+        const uint64_t P = super ? std::min<uint64_t>(*ctx->pinned, kSaturated) : rs[grid.gy];
         st->pair_count = P;
         publish_offsets(st, L, grid, g->n, order, ws);
         if (P >= kSaturated)
@@ -563,8 +584,8 @@ tgs_status tgs_bin_sort(tgs_context* ctx, const tgs_gaussians* g, const tgs_came
         if (P > st->pair_capacity)
             return fail(TGS_ERR_CAPACITY, "%llu pairs needed, capacity %llu",
                         (unsigned long long)P, (unsigned long long)st->pair_capacity);
-        slices = 0;
-        for (int ty = 0; ty < grid.gy; ++ty)
+        if (!super) slices = 0;
+        for (int ty = 0; !super && ty < grid.gy; ++ty)
             slices += (uint64_t(rs[ty + 1] - rs[ty]) + tgs::kSlice - 1) / tgs::kSlice;
     } else {
         // asynchronous: the count stays on the device; the emission and the

@@ -1,4 +1,8 @@
-// Tile-Gaussian pairs in (tile id, depth) order and per-tile ranges (stage (b)).
+// Tile-Gaussian pairs in (tile id, depth) order and per-tile ranges (stage
+// (b)) by tile rows, for grids of more than kSuperMax supertiles (8 x 8
+// tiles; 8K views at tile 16, 4K views at tile 8) or workspaces without room
+// for the supertiles' tables; the others are binned in two levels, which is
+// faster at every size measured (supertile.hip).
 //
 // The order is the one a stable sort of 64-bit (tile << 32 | depth bits) keys
 // produces, built without sorting 64-bit keys and without ever writing the

@@ -28,6 +28,12 @@ constexpr int kScanTile = kScanThreads * kScanItems;
 // binning: pairs per column-sort slice, and the widest tile grid supported
 constexpr int kSlice = 4096;
 constexpr int kMaxCols = 1024;
+// binning in two levels (supertile.hip): Gaussians per block, the most
+// supertiles (8 x 8 tiles) the emission's LDS tables are made for, and about
+// how many chunks the supertiles' lists are cut into
+constexpr int kSuperGauss = 512;
+constexpr int kSuperMax = 1024;
+constexpr uint32_t kChunkTarget = 8192;
 
 enum RecordFlags : uint32_t {
     kClampR = 1u, kClampG = 2u, kClampB = 4u, kCulled = 8u, kFovX = 16u, kFovY = 32u,
@@ -45,8 +51,24 @@ struct Grid {
 
 Grid make_grid(const tgs_camera& cam, const tgs_dilation& dil, int tile);
 
+// Byte offsets of the two-level binning's buffers (supertile.hip); supers is 0
+// where the view is binned by rows (binning.hip).
+struct SuperLayout {
+    int sx, supers;            // supertiles per row and in all
+    uint64_t max_chunks;
+    uint64_t list;             // uint2[capacity], supertile lists: id, tile masks
+    uint64_t table;            // uint32[supers * blocks + 1], entries per (supertile, block), scanned
+    uint64_t sums;             // uint32, the scan's tile sums
+    uint64_t first;            // uint32[supers + 1], first chunk of every supertile
+    uint64_t desc;             // uint4[max_chunks]: supertile, first entry, end entry
+    uint64_t nchunks;          // uint32
+    uint64_t row_total;        // uint32[gy], pairs per tile row
+    uint64_t tcnt;             // uint32[max_chunks][64], entries per tile, then first place
+};
+
 // Byte offsets of the sub-buffers of one view's workspace.
 struct Layout {
+    SuperLayout super;         // overlays the row binning's buffers, ecnt .. col_hist
     uint64_t records, tiles_touched;
     uint64_t rects;            // uint2[n], tile rectangle per Gaussian (packed, empty if culled)
     uint64_t srect;            // uint2[n], the same in depth order
@@ -166,6 +188,9 @@ hipError_t radix_sort(uint32_t* const keys[2], uint32_t* const vals[2], uint64_t
                       bool drop_on = false, uint32_t drop = 0u);
 uint64_t radix_counts_elems(uint64_t count);
 uint64_t radix_kept_offset(uint64_t count);
+// Offset (uint32 words) in counts of a 64-bit word the sort sets to zero and
+// leaves to the caller.
+uint64_t radix_spare_offset();
 
 // Exclusive scan of uint32 (in may equal out); with write_total, out[count]
 // receives the total (out then has count + 1 entries).
@@ -200,6 +225,19 @@ hipError_t launch_col_sort(uint8_t* ws, const Layout& L, const Grid& grid, uint6
 // One-time kernel attributes (the column scatter of the widest grid needs
 // more than 64 KiB of LDS).
 hipError_t prepare_binning_kernels();
+
+// binning in two levels (supertile.hip).  super_layout lays its buffers out
+// from `at` and returns their bytes (0: the grid has too many supertiles).
+// launch_super_counts adds the view's pairs to *pairs (device, zeroed by the
+// depth sort); launch_super_lists writes the pair count, saturated, to
+// row_start[gy], the pairs and the ranges.
+hipError_t prepare_supertile_kernels();
+uint64_t super_layout(SuperLayout& L, uint64_t at, int64_t n, uint64_t cap, const Grid& grid);
+hipError_t launch_super_counts(uint8_t* ws, const Layout& L, const uint32_t* order, int64_t n,
+                               const uint32_t* dcount, unsigned long long* pairs, hipStream_t s);
+hipError_t launch_super_lists(uint8_t* ws, const Layout& L, const uint32_t* order, int64_t n,
+                              const uint32_t* dcount, const unsigned long long* pairs,
+                              const Grid& grid, uint32_t capacity, hipStream_t s);
 
 // One view of a raster launch.
 struct RasterView {

@@ -67,7 +67,8 @@ struct SortArea {
     uint32_t* states;     // [kMaxPasses][tiles][kRadixBuckets]
 };
 
-constexpr uint64_t kAreaHead = kMaxPasses * kRadixBuckets + 8;   // totals, kept, tickets
+// totals, kept, tickets, and (the last two) a 64-bit word for the caller
+constexpr uint64_t kAreaHead = kMaxPasses * kRadixBuckets + 8;
 
 __host__ __device__ inline SortArea sort_area(uint32_t* w) {
     SortArea a;
@@ -462,7 +463,7 @@ hipError_t radix_sort(uint32_t* const keys[2], uint32_t* const vals[2], uint64_t
     const SortArea area = sort_area(counts);
     if (count == 0) {
         *result = 0;
-        return fill_u32(area.kept, 0u, 1, s);
+        return fill_u32(area.total, 0u, kAreaHead, s);
     }
     const uint64_t tiles = (count + kSortTile - 1) / kSortTile;
     const int passes = std::min(radix_sort_passes(bits), kMaxPasses);
@@ -488,5 +489,7 @@ uint64_t radix_kept_offset(uint64_t count) {
     (void)count;
     return uint64_t(kMaxPasses) * kRadixBuckets;
 }
+
+uint64_t radix_spare_offset() { return kAreaHead - 2; }
 
 }  // namespace tgs
