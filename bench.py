@@ -102,7 +102,7 @@ def launch_ppt(tiles, tile=16):
     """Pixels per thread of the library's default launch of `tiles` tiles of
     16 x 16 (the rule tgs_default_launch documents)."""
     assert tile == 16
-    return 4 if tiles >= 6144 else 2 if tiles >= 3072 else 1
+    return 4 if tiles >= 5120 else 2 if tiles >= 3072 else 1
 
 
 def fwd_ops(evals, tested, blended, pixels, wpix):

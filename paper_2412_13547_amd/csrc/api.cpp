@@ -398,8 +398,10 @@ int default_pixels_per_thread(int tile, int64_t tiles) {
     if (tile == 8) return 1;
     // wavefronts per tile at 4 pixels per thread: 1 (T = 16), 4 (T = 32)
     const int64_t waves = tile == 16 ? tiles : 4 * tiles;
-    if (tile == 32) return waves >= 6144 ? 4 : 2;
-    return waves >= 6144 ? 4 : waves >= 3072 ? 2 : 1;
+    // forward + backward, us: 5700 wavefronts 309 with 4 pixels per thread, 337
+    // with 2; 3600: 341 with 4, 291 with 2, 308 with 1; 2040: 233 and 219
+    if (tile == 32) return waves >= 5120 ? 4 : 2;
+    return waves >= 5120 ? 4 : waves >= 3072 ? 2 : 1;
 }
 
 CamDev make_cam(const tgs_camera& c) {

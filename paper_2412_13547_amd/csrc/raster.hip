@@ -10,12 +10,25 @@
 // view they take the tiles heaviest first (the schedule below).  16x16 and 8x8
 // tiles give one pixel per thread, 32x32 tiles a 2x2 block per thread.  The
 // tile's list is staged through LDS B splat records at a time; every pixel
-// walks it front to back (Sec. 3 Eq. 2).
+// walks it front to back (Sec. 3 Eq. 2), and the backward from its last
+// blended entry back to the first, with the forward's arithmetic and decisions
+// (one shared inline routine).
 //
-// The backward replays the forward walk in the same order with the same
-// arithmetic (one shared inline routine), so it takes bit-identical skip and
-// stop decisions and needs no per-pixel state from the forward: the colour
-// still to come behind entry k is image - (colour accumulated up to k).
+// Both kernels are bound by vector instructions per visited (entry,
+// wavefront): on a 3840 x 2160 view of 3M Gaussians at stride 1 the backward
+// issued one per four cycles and SIMD.  What keeps their number down:
+//  - decisions are lane masks in scalar registers, so that combining them is
+//    scalar work (kept as bools they were moved through vector registers at
+//    every branch);
+//  - tests that cannot matter are left out under uniform branches
+//    (splat_plain; in the backward also entries before every pixel's last);
+//  - the backward sums a lane's pixels by columns and rows, applies the
+//    splat's constants to those sums, and takes dL/do as the sum of dL/dpower
+//    over o; a stopped pixel of the forward needs no test of its own.
+// Forward 172 -> 156 us and backward 344 -> 273 us at stride 2 of that view,
+// 456 -> 415 and 1070 -> 870 us at stride 1 (145 vector instructions and 8
+// transcendental ones to an entry and wavefront of 4 pixels a lane in the
+// backward, 176 before).
 #include "common.hpp"
 #include "wave.hpp"
 
@@ -55,12 +68,54 @@ __device__ __forceinline__ float splat_exponent(const float4 ga, const float4 gb
     return fmaf(dx, fmaf(ga.z, dx, t), (gb.x * dy) * dy);
 }
 
-__device__ __forceinline__ bool splat_test(const float4 gb, float p2, float& G, float& raw,
-                                           float& alpha) {
-    G = __builtin_amdgcn_exp2f(p2);
-    raw = gb.y * G;
-    alpha = __builtin_amdgcn_fmed3f(raw, 0.0f, kAlphaMax);   // min(0.99, raw) for raw >= 0
-    return p2 <= 0.0f && raw >= kAlphaMin;
+// Decisions are kept as masks over the wavefront's lanes, in scalar registers:
+// combining them costs no vector instruction, and one that differs between
+// the two sides of a uniform branch stays a mask.
+__device__ __forceinline__ bool lane_of(uint64_t mask) {
+    return __builtin_amdgcn_inverse_ballot_w64(mask);
+}
+
+// The tests of the lanes' pixels k (every lane of the wavefront takes part);
+// `plain` (uniform): the splat is splat_plain.  clamped: o G > 0.99.
+template <int NP>
+__device__ __forceinline__ void splat_test(float o, bool plain, const float* p2, float* alpha,
+                                           uint64_t* hit, uint64_t* clamped) {
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+        alpha[k] = o * __builtin_amdgcn_exp2f(p2[k]);
+        hit[k] = __ballot(alpha[k] >= kAlphaMin);
+        clamped[k] = 0;
+    }
+    if (!plain) {
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            hit[k] &= __ballot(p2[k] <= 0.0f);
+            clamped[k] = __ballot(alpha[k] > kAlphaMax);
+            alpha[k] = __builtin_amdgcn_fmed3f(alpha[k], 0.0f, kAlphaMax);   // min(0.99, o G) for o G >= 0
+        }
+    }
+}
+
+// A uniform LDS byte offset in a vector register, shared by all the reads of
+// an entry (their arrays lie at constant distances).
+__device__ __forceinline__ uint32_t entry_offset(int e) {
+    uint32_t at = uint32_t(e) * 16u;
+    asm("" : "+v"(at));
+    return at;
+}
+
+__device__ __forceinline__ float4 entry_part(const float4* base, uint32_t at) {
+    return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(base) + at);
+}
+
+// A splat whose exponent is never positive and whose alpha never reaches the
+// clamp at any pixel, rounding included: the tests for both can be left out.
+// The form's smaller eigenvalue is at least (4 qa qc - qb^2) / (4 (|qa| +
+// |qc|)) and the exponent's rounding error at most 3.6e-7 (|qa| + |qc|) (dx^2
+// + dy^2), a sixth of what the comparison asks for; o 2^p2 stays below 0.99.
+__device__ __forceinline__ bool splat_plain(const float4 ga, const float4 gb) {
+    const float qa = ga.z, qb = ga.w, qc = gb.x, tr = qa + qc;
+    return qa < 0.0f && qc < 0.0f && 4.0f * qa * qc - qb * qb > 1e-5f * (tr * tr) && gb.y < 0.9899f;
 }
 
 // Exponent below which o 2^p2 < 1/255 for certain: log2(1/255 / o) less a
@@ -195,55 +250,73 @@ __device__ __forceinline__ float swap16_add(float a, float b) {
 // transposing butterfly -- each exchange halves the values a lane keeps: the
 // upper half-wave keeps values 4-7, the odd rows keep the upper two of the
 // remaining four, the upper 8 lanes of a row the second one -- and end with
-// a sum over the 8 lanes of each octet (row mirror, half mirror, quad swaps),
-// so lane 8c (c = 0..7) holds the total of value c.  Value 8 is summed over
-// all lanes the same way and lane 1 keeps it.  Returns the value this lane
-// owns and its index (or -1).
-__device__ __forceinline__ float wave_sum9(const float* v, int& comp) {
+// a sum over the 8 lanes of each octet (half mirror, quad swaps),
+// so lane 8c (c = 0..7) returns the total of value c.  Value 8 is summed
+// within each row of 16 and then across the rows, and lane 63 returns its
+// total.
+__device__ __forceinline__ float wave_sum9(const float* v) {
     const int lane = __lane_id();
-    const bool h16 = lane & 16, h8 = lane & 8;
     float w[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) w[k] = swap32_add(v[k], v[k + 4]);
     const float x0 = swap16_add(w[0], w[2]);
     const float x1 = swap16_add(w[1], w[3]);
-    const float send = h8 ? x0 : x1;
-    float y = (h8 ? x1 : x0) + dpp_f<kDppRowMirror>(send);
+    // x0 of a lane and of the lane 8 on into the lower octets, x1 into the upper
+    float y;
+    asm("s_nop 1\n\tv_add_f32_dpp %0, %1, %1 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %0, %2, %2 row_ror:8 row_mask:0xf bank_mask:0xc\n\ts_nop 1"
+        : "=&v"(y) : "v"(x0), "v"(x1));
+    float z = v[8] + dpp_f<kDppQuadXor1>(v[8]);
     y += dpp_f<kDppRowHalfMirror>(y);
-    y += dpp_f<kDppQuadXor2>(y);
-    y += dpp_f<kDppQuadXor1>(y);
-    float z = swap32_add(v[8], v[8]);
-    z = swap16_add(z, z);
-    z += dpp_f<kDppRowMirror>(z);
-    z += dpp_f<kDppRowHalfMirror>(z);
     z += dpp_f<kDppQuadXor2>(z);
-    z += dpp_f<kDppQuadXor1>(z);
-    comp = -1;
-    if ((lane & 7) == 0) comp = ((lane & 32) ? 4 : 0) + (h16 ? 2 : 0) + (h8 ? 1 : 0);
-    if (lane == 1) {
-        comp = 8;
-        y = z;
-    }
-    return y;
+    y += dpp_f<kDppQuadXor2>(y);
+    z += dpp_f<kDppRowHalfMirror>(z);
+    y += dpp_f<kDppQuadXor1>(y);
+    z += dpp_f<kDppRowMirror>(z);
+    // rows 1 and 3 add the last lane of the row before, then rows 2 and 3 that
+    // of row 1 (the other rows keep z; the nops cover the DPP hazard)
+    asm("s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\t"
+        "s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf"
+        : "+v"(z));
+    return lane == 63 ? z : y;
 }
 
-// Calls entry(e), in order, for the entries e < cnt of an LDS batch whose
-// wavefront mask has this wavefront's bit, while live() holds on some lane:
-// each 64 entries' bits become one ballot, and the wavefront visits the set
-// bits only, so an entry its rectangle cannot reach costs nothing.  Entries
-// after every pixel has stopped change nothing, so leaving early keeps the
-// result.
-template <class L, class F>
-__device__ __forceinline__ void for_wave_entries(const uint32_t* s_m, int cnt, int wave, L&& live,
-                                                 F&& entry) {
-    for (int c = 0; c < cnt; c += 64) {
-        const int q = c + __lane_id();
-        uint64_t m = __ballot(q < cnt && ((s_m[q] >> wave) & 1u));
-        while (m != 0 && __ballot(live()) != 0) {
-            const int e = c + int(__builtin_ctzll(m));
-            m &= m - 1;
-            entry(e);
-        }
+// The sums over a lane's pixels of dp, dp dx, dp dy, dp dx^2, dp dx dy and
+// dp dy^2 (in gv[5], gv[0], gv[1], gv[2], gv[3], gv[4]).  The pixels are PX x
+// PY, so dx takes one value per column and dy one per row: summing dp over
+// the columns and rows first takes 21 operations for 2 x 2 pixels where
+// pixel by pixel takes 34.
+template <class S>
+__device__ __forceinline__ void lane_moments(const float* dp, const float* dx, const float* dy,
+                                             float* gv) {
+    if constexpr (S::NP == 1) {
+        const float x = dp[0] * dx[0], y = dp[0] * dy[0];
+        gv[0] = x;
+        gv[1] = y;
+        gv[2] = x * dx[0];
+        gv[3] = x * dy[0];
+        gv[4] = y * dy[0];
+        gv[5] = dp[0];
+    } else if constexpr (S::NP == 2) {                 // one row of two pixels
+        const float x0 = dp[0] * dx[0], x1 = dp[1] * dx[1], s = dp[0] + dp[1];
+        const float y = s * dy[0];
+        gv[0] = x0 + x1;
+        gv[1] = y;
+        gv[2] = fmaf(x1, dx[1], x0 * dx[0]);
+        gv[3] = gv[0] * dy[0];
+        gv[4] = y * dy[0];
+        gv[5] = s;
+    } else {                                           // pixels 0, 1 above 2, 3
+        const float cA = dp[0] + dp[2], cB = dp[1] + dp[3];
+        const float rA = dp[0] + dp[1], rB = dp[2] + dp[3];
+        const float xA = cA * dx[0], xB = cB * dx[1], yA = rA * dy[0], yB = rB * dy[2];
+        gv[0] = xA + xB;
+        gv[1] = yA + yB;
+        gv[2] = fmaf(xB, dx[1], xA * dx[0]);
+        gv[4] = fmaf(yB, dy[2], yA * dy[0]);
+        const float mA = fmaf(dp[2], dy[2], dp[0] * dy[0]), mB = fmaf(dp[3], dy[2], dp[1] * dy[0]);
+        gv[3] = fmaf(mB, dx[1], mA * dx[0]);
+        gv[5] = rA + rB;
     }
 }
 
@@ -257,12 +330,13 @@ __device__ __forceinline__ void for_wave_entries(const uint32_t* s_m, int cnt, i
 // the floor kTMin > 0, so the sign is never ambiguous, and no per-pixel
 // flag has to be carried from entry to entry.
 template <int T, int PPT, int BATCH, bool COUNTS>
-__global__ void __launch_bounds__((Shape<T, PPT>::NT)) raster_fwd_kernel(RasterViews vt) {
+__global__ void __launch_bounds__((Shape<T, PPT>::NT)) __attribute__((amdgpu_waves_per_eu(8)))
+raster_fwd_kernel(RasterViews vt) {
     using S = Shape<T, PPT>;
-    __shared__ float4 s_a[BATCH], s_b[BATCH];
-    // blue, at the stride of s_a and s_b so one address serves all three
-    __shared__ float4 s_c[BATCH];
-    __shared__ uint32_t s_m[BATCH];                              // wavefronts that look at it
+    // splat constants ga, gb and blue, at one stride so one address serves all
+    __shared__ float4 s_e[3][BATCH];
+    // wavefronts that look at it; bit 31: splat_plain
+    __shared__ uint32_t s_m[BATCH];
     int v;
     int64_t tile;
     if (!locate(vt, blockIdx.x, v, tile)) return;                // block-uniform
@@ -310,61 +384,70 @@ __global__ void __launch_bounds__((Shape<T, PPT>::NT)) raster_fwd_kernel(RasterV
             float4 ga, gb;
             stage_conic(r[0], r1, ga, gb);
             const float thr = skip_threshold(r1.y);
-            s_a[q] = ga;
-            s_b[q] = gb;
-            s_c[q] = make_float4(r[2].x, 0.0f, 0.0f, 0.0f);
-            s_m[q] = wave_mask<S>(ga, gb.x, thr, wr);
+            s_e[0][q] = ga;
+            s_e[1][q] = gb;
+            s_e[2][q] = make_float4(r[2].x, 0.0f, 0.0f, 0.0f);
+            s_m[q] = wave_mask<S>(ga, gb.x, thr, wr) | (splat_plain(ga, gb) ? 1u << 31 : 0u);
         }
         __syncthreads();
         // branch-free per entry: a skipped entry adds exactly 0 and leaves T
-        // (entries no pixel of the wavefront can reach are not visited)
-        auto entry = [&](int e) {
-            bool any = false;
+        // (entries no pixel of the wavefront can reach are not visited).  A
+        // stopped pixel's negative T makes every hit stop it again.
+        auto entry = [&](int e, bool plain) {
             if constexpr (COUNTS) {
 #pragma unroll
                 for (int k = 0; k < S::NP; ++k) ntest[k] += Ts[k] > 0.0f ? 1u : 0u;
             }
-            const float4 a = s_a[e], b = s_b[e];
-            const float bb = s_c[e].x;
-            float dx[S::NP], dy[S::NP], t[S::NP], p2[S::NP];
+            const uint32_t at = entry_offset(e);
+            const float4 a = entry_part(s_e[0], at), b = entry_part(s_e[1], at);
+            const float bb = entry_part(s_e[2], at).x;
+            float dx[S::NP], dy[S::NP], t[S::NP], p2[S::NP], alpha[S::NP];
+            uint64_t hit[S::NP], clamped[S::NP], any = 0;
 #pragma unroll
             for (int k = 0; k < S::NP; ++k) p2[k] = splat_exponent(a, b, X[k], Y[k], dx[k], dy[k], t[k]);
+            splat_test<S::NP>(b.y, plain, p2, alpha, hit, clamped);
+            const uint32_t pos = base - start + uint32_t(e) + 1;
 #pragma unroll
             for (int k = 0; k < S::NP; ++k) {
-                float G, raw, alpha;
-                const bool hit = splat_test(b, p2[k], G, raw, alpha) && Ts[k] > 0.0f;
-                const float w0 = alpha * Ts[k];
+                const float w0 = alpha[k] * Ts[k];
                 // T after this entry below the floor: the pixel stops here;
                 // otherwise it blends (one comparison: stop implies hit)
-                const bool stop = hit && Ts[k] - w0 < kTMin;
-                const bool blend = hit != stop;
-                const float w = blend ? w0 : 0.0f;
+                const uint64_t stop = hit[k] & __ballot(Ts[k] - w0 < kTMin);
+                const uint64_t blend = hit[k] ^ stop;
+                const float w = lane_of(blend) ? w0 : 0.0f;
                 c0[k] = fmaf(b.z, w, c0[k]);
                 c1[k] = fmaf(b.w, w, c1[k]);
                 c2[k] = fmaf(bb, w, c2[k]);
                 const float tn = Ts[k] - w;           // Ts itself when not blending
-                Ts[k] = stop ? -tn : tn;
-                const uint32_t pos = base - start + uint32_t(e) + 1;
-                last[k] = blend ? pos : last[k];
-                any = any || blend;
                 if constexpr (COUNTS) {
-                    nblend[k] += blend ? 1u : 0u;
-                    neval[k] = stop ? pos : neval[k];
+                    nblend[k] += lane_of(blend) ? 1u : 0u;
+                    neval[k] = lane_of(stop) && Ts[k] > 0.0f ? pos : neval[k];
                 }
+                Ts[k] = lane_of(stop) ? -fabsf(tn) : tn;
+                last[k] = lane_of(blend) ? pos : last[k];
+                any |= blend;
             }
-            return __ballot(any) != 0;
+            return any != 0;
         };
-        // the same walk as for_wave_entries, also collecting per 64 entries
-        // the bits of those some pixel of this wavefront blended: they are
-        // all the backward has to visit
+        // the entries of the batch whose wavefront mask has this wavefront's
+        // bit, in order, while some pixel takes entries (looked at every four:
+        // entries after every pixel has stopped change nothing): each 64
+        // entries' bits become one ballot, and the wavefront visits the set
+        // bits only, so an entry its rectangle cannot reach costs nothing.
+        // Per 64 entries it also collects the bits of those some pixel of
+        // this wavefront blended: they are all the backward has to visit.
         for (int c = 0; c < cnt; c += 64) {
             const int q = c + __lane_id();
-            uint64_t m = __ballot(q < cnt && ((s_m[q] >> wave) & 1u));
+            const uint32_t mq = q < cnt ? s_m[q] : 0u;
+            uint64_t m = __ballot((mq >> wave) & 1u);
+            const uint64_t other = m & ~__ballot(mq >> 31);
             uint64_t bm = 0;
-            while (m != 0 && __ballot(live()) != 0) {
+            bool go = __ballot(live()) != 0;
+            for (uint32_t u = 1; m != 0 && go; ++u) {
                 const int j = int(__builtin_ctzll(m));
                 m &= m - 1;
-                if (entry(c + j)) bm |= uint64_t(1) << j;
+                if (entry(c + j, ((other >> j) & 1u) == 0)) bm |= uint64_t(1) << j;
+                if ((u & 3u) == 0u) go = __ballot(live()) != 0;
             }
             if (__lane_id() == 0)                    // entry base + c is chunk (base - start + c) / 64
                 rv.bits[uint64_t(wave) * rv.bits_stride + (start >> 6) + uint64_t(tile) +
@@ -400,27 +483,6 @@ __global__ void __launch_bounds__((Shape<T, PPT>::NT)) raster_fwd_kernel(RasterV
     }
 }
 
-// Calls entry(e), from the last to the first, for the entries e < cnt of an
-// LDS batch that some pixel of this wavefront blended in the forward: the
-// blend bits, one word per 64 entries from word `chunk` on (the batch
-// starts at a multiple of 64 entries of the tile's list).  Without usable
-// bits (a forward with another work split has another wavefront
-// partition) every entry is visited; each pixel still decides its own.
-template <class F>
-__device__ __forceinline__ void for_blended_entries_reverse(const unsigned long long* bits,
-                                                            bool use_bits, uint64_t chunk, int cnt,
-                                                            F&& entry) {
-    for (int c = ((cnt - 1) >> 6) << 6; c >= 0; c -= 64) {
-        uint64_t m = use_bits ? uint64_t(bits[chunk + uint64_t(c >> 6)]) : ~uint64_t(0);
-        if (cnt - c < 64) m &= (uint64_t(1) << (cnt - c)) - 1;
-        while (m != 0) {
-            const int hb = 63 - __builtin_clzll(m);
-            m ^= uint64_t(1) << hb;
-            entry(c + hb);
-        }
-    }
-}
-
 // The blend backward: each pixel walks its list back to front, from the
 // last entry it blended (ws_last) down to the first, starting from its
 // final transmittance (ws_tfinal); both were left by the forward, and so
@@ -448,10 +510,13 @@ __device__ __forceinline__ void for_blended_entries_reverse(const unsigned long 
 //   dL/dA = -1/2 sum dp dx^2,  dL/dB = -sum dp dx dy,  dL/dC = -1/2 sum dp dy^2,
 // with dp = dL/dpower, qa2 = 2 qa, qc2 = 2 qc.
 template <int T, int PPT, int BATCH>
-__global__ void __launch_bounds__((Shape<T, PPT>::NT)) raster_bwd_kernel(RasterViews vt) {
+__global__ void __launch_bounds__((Shape<T, PPT>::NT)) __attribute__((amdgpu_waves_per_eu(7)))
+raster_bwd_kernel(RasterViews vt) {
     using S = Shape<T, PPT>;
-    __shared__ float4 s_a[BATCH], s_b[BATCH], s_c[BATCH];
-    __shared__ uint32_t s_id[BATCH];
+    // splat constants ga, gb and (blue, 2 qa, 2 qc, 1 / o), then where its row
+    // of grad2d begins (in bytes); at one stride so one address serves all
+    __shared__ float4 s_e[4][BATCH];
+    __shared__ uint32_t s_plain[BATCH];                          // splat_plain
     __shared__ uint32_t s_end;                                   // entries the tile walks
     // multi-wavefront tiles add their wavefronts' sums in LDS and flush each
     // batch with one set of global atomics per entry
@@ -482,14 +547,16 @@ __global__ void __launch_bounds__((Shape<T, PPT>::NT)) raster_bwd_kernel(RasterV
     float X[S::NP], Y[S::NP], Ts[S::NP], Sb[S::NP];
     float g0[S::NP], g1[S::NP], g2[S::NP];
     uint32_t last[S::NP];
-    uint32_t lmax = 0;
+    uint32_t lmax = 0, lmin = 0xFFFFFFFFu;
 #pragma unroll
     for (int k = 0; k < S::NP; ++k) {
         const int i = i0 + k % S::PX, j = j0 + k / S::PX;
         const bool in = i < grid.w_ds && j < grid.h_ds;
         X[k] = float(grid.stride * i + grid.off_x);
         Y[k] = float(grid.stride * j + grid.off_y);
-        Ts[k] = 1.0f;
+        // (a pixel that blends nothing: T = 0, so that w and dp are 0 whatever
+        // it is tested on)
+        Ts[k] = 0.0f;
         g0[k] = g1[k] = g2[k] = 0.0f;
         last[k] = 0;
         if (in) {
@@ -497,16 +564,24 @@ __global__ void __launch_bounds__((Shape<T, PPT>::NT)) raster_bwd_kernel(RasterV
             g0[k] = rv.dL[p];
             g1[k] = rv.dL[pix + p];
             g2[k] = rv.dL[2 * pix + p];
-            Ts[k] = rv.ws_tfinal[p];
             last[k] = min(rv.ws_last[p], end - start);
+            if (last[k] != 0u) {
+                Ts[k] = rv.ws_tfinal[p];
+                lmin = min(lmin, last[k]);
+            }
         }
         Sb[k] = fmaf(g2[k], rv.bg[2], fmaf(g1[k], rv.bg[1], g0[k] * rv.bg[0]));
         lmax = max(lmax, last[k]);
     }
     // entries [0, wend) hold every blend of this wavefront's pixels, [0, s_end)
     // those of the tile
-    for (int o = 32; o > 0; o >>= 1) lmax = max(lmax, uint32_t(__shfl_xor(int(lmax), o)));
+    // [0, wall) lies before the last blend of every pixel that blends at all
+    for (int o = 32; o > 0; o >>= 1) {
+        lmax = max(lmax, uint32_t(__shfl_xor(int(lmax), o)));
+        lmin = min(lmin, uint32_t(__shfl_xor(int(lmin), o)));
+    }
     const uint32_t wend = uint32_t(__builtin_amdgcn_readfirstlane(int(lmax)));
+    const uint32_t wall = uint32_t(__builtin_amdgcn_readfirstlane(int(lmin)));
     if (S::NT > 64) {
         if (tid == 0) s_end = 0;
         __syncthreads();
@@ -516,10 +591,11 @@ __global__ void __launch_bounds__((Shape<T, PPT>::NT)) raster_bwd_kernel(RasterV
     const uint32_t tend = S::NT > 64 ? uint32_t(__builtin_amdgcn_readfirstlane(int(s_end))) : wend;
     // factor of the component this lane owns after wave_sum9
     const int lane = __lane_id();
-    const int own = (lane & 7) == 0 ? (lane >> 3) : (lane == 1 ? 8 : -1);
+    const int own = (lane & 7) == 0 ? (lane >> 3) : (lane == 63 ? 8 : -1);
     const float scale = own == 0 || own == 1 ? kLn2
                         : own == 2 || own == 4 ? -0.5f
                         : own == 3 ? -1.0f : 1.0f;
+    char* const mine = reinterpret_cast<char*>(rv.g2d + max(own, 0));   // its component of row 0
     // batches of the list from the back, starting at multiples of BATCH
     const int top = int(tend) == 0 ? -1 : (int(tend) - 1) / BATCH * BATCH;
     for (int lo = top; lo >= 0; lo -= BATCH) {
@@ -530,96 +606,109 @@ __global__ void __launch_bounds__((Shape<T, PPT>::NT)) raster_bwd_kernel(RasterV
             const float4* r = rv.rec + 3 * uint64_t(id);
             float4 ga, gb;
             stage_conic(r[0], r[1], ga, gb);
-            s_a[q] = ga;
-            s_b[q] = gb;
-            s_c[q] = make_float4(r[2].x, ga.z + ga.z, gb.x + gb.x, 0.0f);
-            s_id[q] = id;
+            s_e[0][q] = ga;
+            s_e[1][q] = gb;
+            s_e[2][q] = make_float4(r[2].x, ga.z + ga.z, gb.x + gb.x, 1.0f / gb.y);
+            *reinterpret_cast<uint64_t*>(&s_e[3][q]) = uint64_t(id) * (kGrad2d * 4);
+            s_plain[q] = splat_plain(ga, gb) ? 1u : 0u;
         }
         if constexpr (kBlockSum)
             for (int q = tid; q < cnt * kGrad2d; q += S::NT) s_g[q] = 0.0f;
         __syncthreads();
-        auto entry = [&](int e) {
-            const float4 a = s_a[e], b = s_b[e];
-            const float4 c = s_c[e];                  // (b, qa2, qc2, unused)
+        auto entry = [&](int e, bool plain) {
+            const uint32_t at = entry_offset(e);
+            const float4 a = entry_part(s_e[0], at), b = entry_part(s_e[1], at);
             const uint32_t pos = uint32_t(lo + e);    // 0-based position in the list
             // the forward's skip decisions; blended iff also before the last blend
-            float dx[S::NP], dy[S::NP], t[S::NP], p2[S::NP], G[S::NP], raw[S::NP], alpha[S::NP];
-            bool blend[S::NP];
+            float dx[S::NP], dy[S::NP], t[S::NP], p2[S::NP], alpha[S::NP];
+            uint64_t blend[S::NP], clamped[S::NP];
 #pragma unroll
             for (int k = 0; k < S::NP; ++k) p2[k] = splat_exponent(a, b, X[k], Y[k], dx[k], dy[k], t[k]);
-            bool lane_any = false;                    // a pixel of this lane blends it
+            splat_test<S::NP>(b.y, plain, p2, alpha, blend, clamped);
+            if (pos >= wall) {                        // (uniform)
 #pragma unroll
-            for (int k = 0; k < S::NP; ++k) {
-                blend[k] = splat_test(b, p2[k], G[k], raw[k], alpha[k]) && pos < last[k];
-                lane_any = lane_any || blend[k];
+                for (int k = 0; k < S::NP; ++k) blend[k] &= __ballot(pos < last[k]);
             }
-            if (__ballot(lane_any) == 0) return;      // no pixel of the wavefront blends it
-            float gv[kGrad2d];
+            if (!use_bits) {                          // (with the bits some pixel blends it)
+                uint64_t any = 0;
+#pragma unroll
+                for (int k = 0; k < S::NP; ++k) any |= blend[k];
+                if (any == 0) return;
+            }
+            const float4 c = entry_part(s_e[2], at);  // (b, qa2, qc2, 1 / o)
             // ab = alpha where the pixel blends the entry, 0 elsewhere: then
-            // w, the S update, dp and the G term vanish by themselves (T is
-            // kept by a select, so it never picks up the rounding of a
-            // reciprocal of 1).  The lane's pixels are summed with FMAs.
+            // w, the S update and dp vanish by themselves, and T is divided by
+            // exactly 1 (v_rcp_f32(1) is 1).  dp = dL/dpower.
+            float dp[S::NP], gr = 0.0f, gg = 0.0f, gb = 0.0f;
 #pragma unroll
             for (int k = 0; k < S::NP; ++k) {
-                const float ab = blend[k] ? alpha[k] : 0.0f;
-                const float inv = __builtin_amdgcn_rcpf(1.0f - ab);
-                const float T0 = blend[k] ? Ts[k] * inv : Ts[k];    // in front of the entry
+                const float ab = lane_of(blend[k]) ? alpha[k] : 0.0f;
+                const float T0 = Ts[k] * __builtin_amdgcn_rcpf(1.0f - ab);    // in front of the entry
                 const float w = ab * T0;
                 // dL/dalpha = T0 (sum_c dL/dC_c rgb_c - S)
-                const float gcol = fmaf(g2[k], c.x, fmaf(g1[k], b.w, g0[k] * b.z));
-                const float diff = gcol - Sb[k];
-                const float dal = T0 * diff;
+                const float diff = fmaf(g2[k], c.x, fmaf(g1[k], b.w, fmaf(g0[k], b.z, -Sb[k])));
                 Sb[k] = fmaf(ab, diff, Sb[k]);
-                // no gradient through the 0.99 clamp
-                const bool live = blend[k] && !(raw[k] > kAlphaMax);
-                const float dp = (live ? alpha[k] : 0.0f) * dal;
-                const float Gl = live ? G[k] : 0.0f;
-                const float pdx = dp * dx[k], pdy = dp * dy[k];
-                if (k == 0) {
-                    gv[0] = pdx;
-                    gv[1] = pdy;
-                    gv[2] = pdx * dx[k];
-                    gv[3] = pdx * dy[k];
-                    gv[4] = pdy * dy[k];
-                    gv[5] = Gl * dal;
-                    gv[6] = w * g0[k];
-                    gv[7] = w * g1[k];
-                    gv[8] = w * g2[k];
-                } else {
-                    gv[0] += pdx;
-                    gv[1] += pdy;
-                    gv[2] = fmaf(pdx, dx[k], gv[2]);
-                    gv[3] = fmaf(pdx, dy[k], gv[3]);
-                    gv[4] = fmaf(pdy, dy[k], gv[4]);
-                    gv[5] = fmaf(Gl, dal, gv[5]);
-                    gv[6] = fmaf(w, g0[k], gv[6]);
-                    gv[7] = fmaf(w, g1[k], gv[7]);
-                    gv[8] = fmaf(w, g2[k], gv[8]);
-                }
+                dp[k] = w * diff;
+                gr = k == 0 ? w * g0[k] : fmaf(w, g0[k], gr);
+                gg = k == 0 ? w * g1[k] : fmaf(w, g1[k], gg);
+                gb = k == 0 ? w * g2[k] : fmaf(w, g2[k], gb);
                 Ts[k] = T0;
             }
-            int comp;
-            float sum = wave_sum9(gv, comp);
-            // lanes 0 and 8 hold Sx and Sy: exchange them (rotation by 8
-            // within a row of 16 lanes) to form the u and v components
-            const float other = dpp_f<kDppRowRor8>(sum);
-            if (comp == 0) sum = fmaf(c.y, sum, a.w * other);
-            if (comp == 1) sum = fmaf(c.z, sum, a.w * other);
-            if (comp >= 0 && sum != 0.0f) {
-                if constexpr (kBlockSum) atomicAdd(&s_g[e * kGrad2d + comp], sum * scale);
-                else atomicAdd(&rv.g2d[uint64_t(s_id[e]) * kGrad2d + comp], sum * scale);
+            if (!plain) {                             // no gradient through the 0.99 clamp
+#pragma unroll
+                for (int k = 0; k < S::NP; ++k) dp[k] = lane_of(clamped[k]) ? 0.0f : dp[k];
+            }
+            // the lane's moments of dp, over its columns and rows of pixels, and
+            // with the splat's constants dL/du, dL/dv and dL/do = sum dp / o
+            float gv[kGrad2d];
+            lane_moments<S>(dp, dx, dy, gv);
+            const float mx = gv[0], my = gv[1];
+            gv[0] = fmaf(c.y, mx, a.w * my);
+            gv[1] = fmaf(c.z, my, a.w * mx);
+            gv[5] *= c.w;
+            gv[6] = gr;
+            gv[7] = gg;
+            gv[8] = gb;
+            float sum = wave_sum9(gv) * scale;
+            asm volatile("" : "+v"(sum));             // (summed by all lanes, not below)
+            if (own >= 0) {
+                if constexpr (kBlockSum) {
+                    atomicAdd(&s_g[e * kGrad2d + own], sum);
+                } else {
+                    const uint64_t row = *reinterpret_cast<const uint64_t*>(
+                        reinterpret_cast<const char*>(s_e[3]) + at);
+                    atomicAdd(reinterpret_cast<float*>(mine + row), sum);
+                }
             }
         };
-        // entries at or past this wavefront's last blend change nothing
+        // from the last to the first, the entries that some pixel of this
+        // wavefront blended in the forward: the blend bits, one word per 64
+        // entries (the batch starts at a multiple of 64 entries of the tile's
+        // list).  Without usable bits (a forward with another work split has
+        // another wavefront partition) every entry is visited; each pixel
+        // still decides its own.  Entries at or past this wavefront's last
+        // blend change nothing.
         const int wcnt = min(cnt, max(0, int(wend) - lo));
-        for_blended_entries_reverse(wbits, use_bits, (start >> 6) + uint64_t(tile) + uint64_t(lo / 64),
-                                    wcnt, entry);
+        const uint64_t chunk = (start >> 6) + uint64_t(tile) + uint64_t(lo / 64);
+        for (int c = ((wcnt - 1) >> 6) << 6; c >= 0; c -= 64) {
+            uint64_t m = use_bits ? uint64_t(wbits[chunk + uint64_t(c >> 6)]) : ~uint64_t(0);
+            if (wcnt - c < 64) m &= (uint64_t(1) << (wcnt - c)) - 1;
+            const int q = c + lane;
+            const uint64_t other = m & ~__ballot(q < cnt && s_plain[q] != 0u);
+            while (m != 0) {
+                const int hb = 63 - __builtin_clzll(m);
+                m ^= uint64_t(1) << hb;
+                entry(c + hb, ((other >> hb) & 1u) == 0);
+            }
+        }
         if constexpr (kBlockSum) {
             __syncthreads();
             for (int q = tid; q < cnt * kGrad2d; q += S::NT) {
                 const float g = s_g[q];
                 if (g != 0.0f)
-                    atomicAdd(&rv.g2d[uint64_t(s_id[q / kGrad2d]) * kGrad2d + q % kGrad2d], g);
+                    atomicAdd(reinterpret_cast<float*>(reinterpret_cast<char*>(rv.g2d) +
+                                                       *reinterpret_cast<const uint64_t*>(&s_e[3][q / kGrad2d])) +
+                                  q % kGrad2d, g);
             }
         }
     }
