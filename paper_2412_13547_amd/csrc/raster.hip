@@ -250,7 +250,7 @@ __device__ __forceinline__ float swap16_add(float a, float b) {
 // transposing butterfly -- each exchange halves the values a lane keeps: the
 // upper half-wave keeps values 4-7, the odd rows keep the upper two of the
 // remaining four, the upper 8 lanes of a row the second one -- and end with
-// a sum over the 8 lanes of each octet (half mirror, quad swaps),
+// a sum over the 8 lanes of each octet (row mirror, half mirror, quad swaps),
 // so lane 8c (c = 0..7) returns the total of value c.  Value 8 is summed
 // within each row of 16 and then across the rows, and lane 63 returns its
 // total.
@@ -261,11 +261,9 @@ __device__ __forceinline__ float wave_sum9(const float* v) {
     for (int k = 0; k < 4; ++k) w[k] = swap32_add(v[k], v[k + 4]);
     const float x0 = swap16_add(w[0], w[2]);
     const float x1 = swap16_add(w[1], w[3]);
-    // x0 of a lane and of the lane 8 on into the lower octets, x1 into the upper
-    float y;
-    asm("s_nop 1\n\tv_add_f32_dpp %0, %1, %1 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %0, %2, %2 row_ror:8 row_mask:0xf bank_mask:0xc\n\ts_nop 1"
-        : "=&v"(y) : "v"(x0), "v"(x1));
+    const bool h8 = lane & 8;
+    const float send = h8 ? x0 : x1;
+    float y = (h8 ? x1 : x0) + dpp_f<kDppRowMirror>(send);
     float z = v[8] + dpp_f<kDppQuadXor1>(v[8]);
     y += dpp_f<kDppRowHalfMirror>(y);
     z += dpp_f<kDppQuadXor2>(z);
@@ -501,14 +499,12 @@ raster_fwd_kernel(RasterViews vt) {
 // forward's inline routine; an entry is blended iff it passes them and lies
 // before the pixel's last blended entry.
 //
-// Per blended entry the lane's contribution to the nine sums, as moments
-// that the wave reduces first; the splat's constants and the constant
-// factors of each component (ln 2 for u and v, -1/2, -1, -1/2 for A, B, C)
-// are applied once per wave to the reduced sums:
+// Per blended entry the lane's contribution to the nine sums, as moments:
 //   dL/du = ln2 (qa2 Sx + qb Sy),  dL/dv = ln2 (qc2 Sy + qb Sx),
-//   Sx = sum dp dx,  Sy = sum dp dy,
+//   Sx = sum dp dx,  Sy = sum dp dy,  dL/do = sum dp / o,
 //   dL/dA = -1/2 sum dp dx^2,  dL/dB = -sum dp dx dy,  dL/dC = -1/2 sum dp dy^2,
-// with dp = dL/dpower, qa2 = 2 qa, qc2 = 2 qc.
+// with dp = dL/dpower, qa2 = 2 qa, qc2 = 2 qc; the constant factors are applied
+// once per wave to the reduced sums.
 template <int T, int PPT, int BATCH>
 __global__ void __launch_bounds__((Shape<T, PPT>::NT)) __attribute__((amdgpu_waves_per_eu(7)))
 raster_bwd_kernel(RasterViews vt) {
@@ -646,9 +642,15 @@ raster_bwd_kernel(RasterViews vt) {
                 const float T0 = Ts[k] * __builtin_amdgcn_rcpf(1.0f - ab);    // in front of the entry
                 const float w = ab * T0;
                 // dL/dalpha = T0 (sum_c dL/dC_c rgb_c - S)
-                const float diff = fmaf(g2[k], c.x, fmaf(g1[k], b.w, fmaf(g0[k], b.z, -Sb[k])));
+                float diff;
+                if constexpr (S::NP == 1) {
+                    diff = fmaf(g2[k], c.x, fmaf(g1[k], b.w, g0[k] * b.z)) - Sb[k];
+                    dp[k] = ab * (T0 * diff);
+                } else {                              // two operations fewer
+                    diff = fmaf(g2[k], c.x, fmaf(g1[k], b.w, fmaf(g0[k], b.z, -Sb[k])));
+                    dp[k] = w * diff;
+                }
                 Sb[k] = fmaf(ab, diff, Sb[k]);
-                dp[k] = w * diff;
                 gr = k == 0 ? w * g0[k] : fmaf(w, g0[k], gr);
                 gg = k == 0 ? w * g1[k] : fmaf(w, g1[k], gg);
                 gb = k == 0 ? w * g2[k] : fmaf(w, g2[k], gb);
@@ -659,17 +661,30 @@ raster_bwd_kernel(RasterViews vt) {
                 for (int k = 0; k < S::NP; ++k) dp[k] = lane_of(clamped[k]) ? 0.0f : dp[k];
             }
             // the lane's moments of dp, over its columns and rows of pixels, and
-            // with the splat's constants dL/du, dL/dv and dL/do = sum dp / o
+            // with the splat's constants dL/du, dL/dv and dL/do = sum dp / o.
+            // (With one pixel a lane, on small views, the kernel waits for its
+            // chain of entries and not for instructions: there the constants
+            // go to the sums, which cancel less.)
             float gv[kGrad2d];
             lane_moments<S>(dp, dx, dy, gv);
-            const float mx = gv[0], my = gv[1];
-            gv[0] = fmaf(c.y, mx, a.w * my);
-            gv[1] = fmaf(c.z, my, a.w * mx);
+            if constexpr (S::NP > 1) {
+                const float mx = gv[0], my = gv[1];
+                gv[0] = fmaf(c.y, mx, a.w * my);
+                gv[1] = fmaf(c.z, my, a.w * mx);
+            }
             gv[5] *= c.w;
             gv[6] = gr;
             gv[7] = gg;
             gv[8] = gb;
-            float sum = wave_sum9(gv) * scale;
+            float sum = wave_sum9(gv);
+            if constexpr (S::NP == 1) {
+                // lanes 0 and 8 hold Sx and Sy: exchange them (rotation by 8
+                // within a row of 16 lanes)
+                const float cross = a.w * dpp_f<kDppRowRor8>(sum);
+                sum = own == 0 ? fmaf(c.y, sum, cross) : sum;
+                sum = own == 1 ? fmaf(c.z, sum, cross) : sum;
+            }
+            sum *= scale;
             asm volatile("" : "+v"(sum));             // (summed by all lanes, not below)
             if (own >= 0) {
                 if constexpr (kBlockSum) {
