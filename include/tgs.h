@@ -236,7 +236,8 @@ tgs_status tgs_query_sizes(int64_t n, const tgs_camera* cam, const tgs_dilation*
  * pixels per thread written to *lds_batch and *pixels_per_thread, for a
  * launch of many tiles.  A launch whose tiles (all its views') would leave
  * SIMDs idle gets fewer pixels per thread: at T = 16, 2 below 5120 tiles and
- * 1 below 3072; at T = 32, 2 below 1280.  Results do not depend on it.
+ * 1 below 3072; at T = 32, 2 below 1280; and an LDS batch of at least a
+ * record per thread, up to 256.  Results do not depend on it.
  * Returns TGS_ERR_INVALID_ARG for a tile other than 8, 16 or 32 or a NULL
  * output. */
 tgs_status tgs_default_launch(int32_t tile, int32_t* lds_batch, int32_t* pixels_per_thread);

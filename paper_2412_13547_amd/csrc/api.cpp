@@ -254,8 +254,8 @@ void add_raster_view(tgs::RasterViews& t, const tgs::RasterView& v) {
     ++t.count;
 }
 
-int lds_batch_of(const tgs_options& opt) {
-    return opt.lds_batch ? opt.lds_batch : tgs::default_lds_batch(opt.tile);
+int lds_batch_of(const tgs_options& opt, int ppt) {
+    return opt.lds_batch ? opt.lds_batch : tgs::default_lds_batch(opt.tile, ppt);
 }
 
 int ppt_of(const tgs_options& opt, int64_t tiles) {
@@ -391,6 +391,15 @@ Layout make_layout(int64_t n, uint64_t cap, const Grid& grid) {
 // Fastest settings measured by the launch autotuner on a batch of 12 views
 // (2M Gaussians) and at the 4K dilated scene (3M Gaussians, stride 2).
 int default_lds_batch(int tile) { return tile == 8 ? 128 : tile == 16 ? 64 : 256; }
+
+// A round stages at least a record per thread: with fewer pixels per thread
+// there are more threads, and rounds of 64 records leave most of them waiting
+// (forward + backward, us, rounds of 64 / 128 / 256: 335 / 291 / 264 at one
+// pixel per thread and 2040 tiles, 287 / 257 / 237 at 468 tiles; 292 / 269 /
+// 298 at two and 3600 tiles; 388 / 391 / 515 at four and 8160 tiles).
+int default_lds_batch(int tile, int ppt) {
+    return std::max(default_lds_batch(tile), std::min(256, tile * tile / ppt));
+}
 
 int default_pixels_per_thread(int tile) { return tile == 8 ? 1 : 4; }
 
@@ -625,7 +634,8 @@ tgs_status tgs_raster_fwd(tgs_context* ctx, const tgs_camera* cam, const tgs_dil
     v.n_blend = n_blend;
     tgs::RasterViews t{};
     add_raster_view(t, v);
-    TGS_HIP(tgs::launch_raster_fwd(opt->tile, ppt_of(*opt, grid.num_tiles()), lds_batch_of(*opt), t,
+    const int ppt = ppt_of(*opt, grid.num_tiles());
+    TGS_HIP(tgs::launch_raster_fwd(opt->tile, ppt, lds_batch_of(*opt, ppt), t,
                                    static_cast<hipStream_t>(stream)));
     return TGS_OK;
 }
@@ -706,8 +716,8 @@ tgs_status tgs_raster_bwd(tgs_context* ctx, const tgs_camera* cam, const tgs_dil
     TGS_HIP(tgs::fill_u32(reinterpret_cast<uint32_t*>(v.g2d), 0u, uint64_t(n) * tgs::kGrad2d, strm));
     tgs::RasterViews t{};
     add_raster_view(t, v);
-    TGS_HIP(tgs::launch_raster_bwd(opt->tile, ppt_of(*opt, grid.num_tiles()), lds_batch_of(*opt), t,
-                                   strm));
+    const int ppt = ppt_of(*opt, grid.num_tiles());
+    TGS_HIP(tgs::launch_raster_bwd(opt->tile, ppt, lds_batch_of(*opt, ppt), t, strm));
     return TGS_OK;
 }
 
@@ -918,7 +928,8 @@ tgs_status tgs_batch_raster_fwd(tgs_context* ctx, int64_t n, int32_t views, cons
         rv.n_tested = io[v].n_tested;
         add_raster_view(rt, rv);
     }
-    TGS_HIP(tgs::launch_raster_fwd(opt->tile, ppt_of(*opt, rt.first_block[rt.count]), lds_batch_of(*opt), rt,
+    const int ppt = ppt_of(*opt, rt.first_block[rt.count]);
+    TGS_HIP(tgs::launch_raster_fwd(opt->tile, ppt, lds_batch_of(*opt, ppt), rt,
                                    static_cast<hipStream_t>(stream)));
     return TGS_OK;
 }
@@ -978,8 +989,8 @@ tgs_status tgs_batch_raster_bwd(tgs_context* ctx, int64_t n, int32_t views, cons
         TGS_HIP(tgs::fill_u32(reinterpret_cast<uint32_t*>(rv.g2d), 0u, uint64_t(n) * tgs::kGrad2d, strm));
         add_raster_view(rt, rv);
     }
-    TGS_HIP(tgs::launch_raster_bwd(opt->tile, ppt_of(*opt, rt.first_block[rt.count]), lds_batch_of(*opt), rt,
-                                   strm));
+    const int ppt = ppt_of(*opt, rt.first_block[rt.count]);
+    TGS_HIP(tgs::launch_raster_bwd(opt->tile, ppt, lds_batch_of(*opt, ppt), rt, strm));
     return TGS_OK;
 }
 

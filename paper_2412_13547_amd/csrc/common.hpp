@@ -278,6 +278,7 @@ static_assert(sizeof(RasterViews) <= 3584, "raster view table too large for kern
 // (64, 128 or 256) and pixels per thread (T = 8: 1; T = 16: 1, 2, 4;
 // T = 32: 2, 4).  Results do not depend on either.
 int default_lds_batch(int tile);
+int default_lds_batch(int tile, int ppt);      // of a launch with that work split
 int default_pixels_per_thread(int tile);
 // The default work split of a launch over `tiles` tiles (all its views'):
 // fewer pixels per thread, hence more wavefronts per tile, when the tiles
