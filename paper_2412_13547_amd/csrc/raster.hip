@@ -108,6 +108,54 @@ __device__ __forceinline__ float4 entry_part(const float4* base, uint32_t at) {
     return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(base) + at);
 }
 
+// The number of lanes below this one in the mask.
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
+    return __builtin_amdgcn_mbcnt_hi(uint32_t(mask >> 32),
+                                     __builtin_amdgcn_mbcnt_lo(uint32_t(mask), 0u));
+}
+
+// LDS written by lanes of this wavefront is read by others of it.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// One pixel a lane (views of few tiles): a wavefront's time is a chain of
+// entries, so what an entry waits for counts, and there are registers to
+// spare.  The entries it visits are listed in LDS, and it takes them in pairs,
+// without a branch: the constants of one pair are read while the other is
+// blended, and the two entries of a pair fill each other's latencies.  On a
+// wavefront's own a visited entry takes ~230 cycles in the forward and ~480 in
+// the backward; scanning its bits entry by entry, with the reads waited for and
+// the tests under branches, they took 390 and 750.  412 x 274 pixels of
+// 200K Gaussians: forward 94 -> 70 us, backward 140 -> 103; 128 x 128 of 2K:
+// 24.6 -> 18.9 and 39 -> 28; 960 x 540 of 3M (2040 tiles): 100 -> 84 and
+// 158 -> 159.  With two pixels a lane there are more wavefronts than that and
+// the longer code gains nothing (102 -> 102 and 170 -> 187 at 3600 tiles).
+constexpr int kListStep = 4;                           // entries from one look at the pixels to the next
+constexpr int kListPad = 8;                            // entries past the end that a step may read
+struct EntryPair {
+    float4 a[2], b[2], c[2];
+    float blue[2];
+    uint32_t at[2];                                    // LDS offsets
+    // entries i and i + 1 of the list the lanes hold; CONSTS: all of s_e[2], not
+    // the blue alone
+    template <bool CONSTS, class E>
+    __device__ __forceinline__ void load(const E& s_e, uint32_t list, uint32_t i) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            at[u] = uint32_t(__builtin_amdgcn_readlane(int(list), int(i) + u));
+            uint32_t v = at[u];
+            asm("" : "+v"(v));
+            a[u] = entry_part(s_e[0], v);
+            b[u] = entry_part(s_e[1], v);
+            if constexpr (CONSTS) c[u] = entry_part(s_e[2], v);
+            else blue[u] = entry_part(s_e[2], v).x;
+        }
+    }
+};
+
 // A splat whose exponent is never positive and whose alpha never reaches the
 // clamp at any pixel, rounding included: the tests for both can be left out.
 // The form's smaller eigenvalue is at least (4 qa qc - qb^2) / (4 (|qa| +
@@ -331,8 +379,12 @@ template <int T, int PPT, int BATCH, bool COUNTS>
 __global__ void __launch_bounds__((Shape<T, PPT>::NT)) __attribute__((amdgpu_waves_per_eu(8)))
 raster_fwd_kernel(RasterViews vt) {
     using S = Shape<T, PPT>;
+    constexpr bool kListed = PPT == 1;
     // splat constants ga, gb and blue, at one stride so one address serves all
-    __shared__ float4 s_e[3][BATCH];
+    // (kListed: and an entry of zeros, which blends nothing)
+    __shared__ float4 s_e[3][BATCH + kListed];
+    __shared__ uint16_t s_list[kListed ? S::NT / 64 : 1][kListed ? BATCH + 64 : 1];
+    __shared__ uint8_t s_blend[kListed ? S::NT / 64 : 1][kListed ? BATCH : 1];
     // wavefronts that look at it; bit 31: splat_plain
     __shared__ uint32_t s_m[BATCH];
     int v;
@@ -371,6 +423,8 @@ raster_fwd_kernel(RasterViews vt) {
         for (int k = 0; k < S::NP; ++k) l = l || Ts[k] > 0.0f;
         return l;
     };
+    const int lane = __lane_id();
+    if (kListed && tid < 3) s_e[tid][BATCH] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     uint32_t base = start;
     for (; base < end; base += BATCH) {
         if (__syncthreads_count(live()) == 0) break;
@@ -388,6 +442,44 @@ raster_fwd_kernel(RasterViews vt) {
             s_m[q] = wave_mask<S>(ga, gb.x, thr, wr) | (splat_plain(ga, gb) ? 1u << 31 : 0u);
         }
         __syncthreads();
+        // two entries (kListed), with the arithmetic of the one below: alpha is
+        // 0 where an entry is skipped, so that one comparison with the floor
+        // decides (a live T is at least the floor, a stopped one negative: a
+        // skipped entry keeps either).  `bit` in the result: the first is
+        // blended by some pixel; the bit above it, the second.
+        auto pair = [&](const EntryPair& g, uint64_t bit) {
+            float alpha[2];
+            uint64_t hit[2], clamped;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                float dx, dy, t;
+                const float p2 = splat_exponent(g.a[u], g.b[u], X[0], Y[0], dx, dy, t);
+                splat_test<1>(g.b[u].y, false, &p2, alpha + u, hit + u, &clamped);
+                alpha[u] = lane_of(hit[u]) ? alpha[u] : 0.0f;
+            }
+            uint64_t blended = 0;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const uint32_t pos = base - start + (g.at[u] >> 4) + 1;
+                if constexpr (COUNTS) ntest[0] += g.at[u] < BATCH * 16 && Ts[0] > 0.0f ? 1u : 0u;
+                const float w0 = alpha[u] * Ts[0];
+                const float tn = Ts[0] - w0;
+                const bool stops = tn < kTMin;
+                const uint64_t blend = hit[u] & ~__ballot(stops);
+                if constexpr (COUNTS) {
+                    nblend[0] += lane_of(blend) ? 1u : 0u;
+                    neval[0] = stops && Ts[0] > 0.0f ? pos : neval[0];
+                }
+                const float w = stops ? 0.0f : w0;
+                Ts[0] = stops ? -fabsf(Ts[0]) : tn;
+                c0[0] = fmaf(g.b[u].z, w, c0[0]);
+                c1[0] = fmaf(g.b[u].w, w, c1[0]);
+                c2[0] = fmaf(g.blue[u], w, c2[0]);
+                last[0] = lane_of(blend) ? pos : last[0];
+                blended |= blend != 0 ? bit << u : 0;
+            }
+            return blended;
+        };
         // branch-free per entry: a skipped entry adds exactly 0 and leaves T
         // (entries no pixel of the wavefront can reach are not visited).  A
         // stopped pixel's negative T makes every hit stop it again.
@@ -427,6 +519,48 @@ raster_fwd_kernel(RasterViews vt) {
             }
             return any != 0;
         };
+        if constexpr (kListed) {
+            // the entries of the batch whose wavefront mask has this
+            // wavefront's bit (below), in order: their LDS offsets, then the
+            // entry of zeros
+            uint32_t n = 0;
+#pragma unroll
+            for (int c = 0; c < BATCH; c += 64) {
+                const int q = c + lane;
+                const bool sel = q < cnt && ((s_m[q] >> wave) & 1u) != 0u;
+                const uint64_t m = __ballot(sel);
+                if (sel) s_list[wave][n + lanes_below(m)] = uint16_t(q * 16);
+                n += uint32_t(__builtin_popcountll(m));
+                s_blend[wave][q] = 0;
+            }
+            if (lane < kListPad) s_list[wave][n + uint32_t(lane)] = uint16_t(BATCH * 16);
+            wave_lds_sync();
+            bool go = __ballot(live()) != 0;
+            for (uint32_t b0 = 0; b0 < n && go; b0 += 64) {
+                const uint32_t nb = min(64u, n - b0);
+                const uint32_t at = s_list[wave][b0 + uint32_t(lane)];
+                uint64_t bm = 0, bit = 1;
+                EntryPair g0, g1;
+                g0.load<false>(s_e, at, 0);
+                for (uint32_t i = 0; i < nb && go; i += kListStep) {
+                    g1.load<false>(s_e, at, i + 2);
+                    bm |= pair(g0, bit);
+                    g0.load<false>(s_e, at, (i + kListStep) & 63u);
+                    bm |= pair(g1, bit << 2);
+                    bit <<= kListStep;
+                    go = __ballot(live()) != 0;
+                }
+                if ((bm >> lane) & 1u) s_blend[wave][at >> 4] = 1;
+            }
+            wave_lds_sync();
+            for (int c = 0; c < cnt; c += 64) {
+                const uint64_t bm = __ballot(s_blend[wave][c + lane] != 0);
+                if (lane == 0)                       // entry base + c is chunk (base - start + c) / 64
+                    rv.bits[uint64_t(wave) * rv.bits_stride + (start >> 6) + uint64_t(tile) +
+                            (base - start + uint32_t(c)) / 64u] = bm;
+            }
+            continue;
+        }
         // the entries of the batch whose wavefront mask has this wavefront's
         // bit, in order, while some pixel takes entries (looked at every four:
         // entries after every pixel has stopped change nothing): each 64
@@ -509,15 +643,18 @@ template <int T, int PPT, int BATCH>
 __global__ void __launch_bounds__((Shape<T, PPT>::NT)) __attribute__((amdgpu_waves_per_eu(7)))
 raster_bwd_kernel(RasterViews vt) {
     using S = Shape<T, PPT>;
-    // splat constants ga, gb and (blue, 2 qa, 2 qc, 1 / o), then where its row
-    // of grad2d begins (in bytes); at one stride so one address serves all
-    __shared__ float4 s_e[4][BATCH];
-    __shared__ uint32_t s_plain[BATCH];                          // splat_plain
+    constexpr bool kListed = PPT == 1;
+    // splat constants ga, gb and (blue, 2 qa, 2 qc, 1 / o), at one stride so one
+    // address serves all (kListed: and an entry of zeros, which blends nothing)
+    __shared__ float4 s_e[3][BATCH + kListed];
+    __shared__ uint64_t s_row[BATCH];                            // its row of grad2d, in bytes
+    __shared__ uint16_t s_list[kListed ? S::NT / 64 : 1][kListed ? BATCH + 64 : 1];
+    __shared__ uint32_t s_plain[kListed ? 1 : BATCH];            // splat_plain
     __shared__ uint32_t s_end;                                   // entries the tile walks
     // multi-wavefront tiles add their wavefronts' sums in LDS and flush each
     // batch with one set of global atomics per entry
     constexpr bool kBlockSum = S::NT > 64;
-    __shared__ float s_g[kBlockSum ? BATCH * kGrad2d : 1];
+    __shared__ float s_g[kBlockSum ? (BATCH + kListed) * kGrad2d : 1];
     int v;
     int64_t tile;
     if (!locate(vt, blockIdx.x, v, tile)) return;                // block-uniform
@@ -592,6 +729,7 @@ raster_bwd_kernel(RasterViews vt) {
                         : own == 2 || own == 4 ? -0.5f
                         : own == 3 ? -1.0f : 1.0f;
     char* const mine = reinterpret_cast<char*>(rv.g2d + max(own, 0));   // its component of row 0
+    if (kListed && tid < 3) s_e[tid][BATCH] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     // batches of the list from the back, starting at multiples of BATCH
     const int top = int(tend) == 0 ? -1 : (int(tend) - 1) / BATCH * BATCH;
     for (int lo = top; lo >= 0; lo -= BATCH) {
@@ -605,8 +743,8 @@ raster_bwd_kernel(RasterViews vt) {
             s_e[0][q] = ga;
             s_e[1][q] = gb;
             s_e[2][q] = make_float4(r[2].x, ga.z + ga.z, gb.x + gb.x, 1.0f / gb.y);
-            *reinterpret_cast<uint64_t*>(&s_e[3][q]) = uint64_t(id) * (kGrad2d * 4);
-            s_plain[q] = splat_plain(ga, gb) ? 1u : 0u;
+            s_row[q] = uint64_t(id) * (kGrad2d * 4);
+            if constexpr (!kListed) s_plain[q] = splat_plain(ga, gb) ? 1u : 0u;
         }
         if constexpr (kBlockSum)
             for (int q = tid; q < cnt * kGrad2d; q += S::NT) s_g[q] = 0.0f;
@@ -642,14 +780,8 @@ raster_bwd_kernel(RasterViews vt) {
                 const float T0 = Ts[k] * __builtin_amdgcn_rcpf(1.0f - ab);    // in front of the entry
                 const float w = ab * T0;
                 // dL/dalpha = T0 (sum_c dL/dC_c rgb_c - S)
-                float diff;
-                if constexpr (S::NP == 1) {
-                    diff = fmaf(g2[k], c.x, fmaf(g1[k], b.w, g0[k] * b.z)) - Sb[k];
-                    dp[k] = ab * (T0 * diff);
-                } else {                              // two operations fewer
-                    diff = fmaf(g2[k], c.x, fmaf(g1[k], b.w, fmaf(g0[k], b.z, -Sb[k])));
-                    dp[k] = w * diff;
-                }
+                const float diff = fmaf(g2[k], c.x, fmaf(g1[k], b.w, fmaf(g0[k], b.z, -Sb[k])));
+                dp[k] = w * diff;
                 Sb[k] = fmaf(ab, diff, Sb[k]);
                 gr = k == 0 ? w * g0[k] : fmaf(w, g0[k], gr);
                 gg = k == 0 ? w * g1[k] : fmaf(w, g1[k], gg);
@@ -662,58 +794,147 @@ raster_bwd_kernel(RasterViews vt) {
             }
             // the lane's moments of dp, over its columns and rows of pixels, and
             // with the splat's constants dL/du, dL/dv and dL/do = sum dp / o.
-            // (With one pixel a lane, on small views, the kernel waits for its
-            // chain of entries and not for instructions: there the constants
-            // go to the sums, which cancel less.)
             float gv[kGrad2d];
             lane_moments<S>(dp, dx, dy, gv);
-            if constexpr (S::NP > 1) {
-                const float mx = gv[0], my = gv[1];
-                gv[0] = fmaf(c.y, mx, a.w * my);
-                gv[1] = fmaf(c.z, my, a.w * mx);
-            }
+            const float mx = gv[0], my = gv[1];
+            gv[0] = fmaf(c.y, mx, a.w * my);
+            gv[1] = fmaf(c.z, my, a.w * mx);
             gv[5] *= c.w;
             gv[6] = gr;
             gv[7] = gg;
             gv[8] = gb;
             float sum = wave_sum9(gv);
-            if constexpr (S::NP == 1) {
-                // lanes 0 and 8 hold Sx and Sy: exchange them (rotation by 8
-                // within a row of 16 lanes)
-                const float cross = a.w * dpp_f<kDppRowRor8>(sum);
-                sum = own == 0 ? fmaf(c.y, sum, cross) : sum;
-                sum = own == 1 ? fmaf(c.z, sum, cross) : sum;
-            }
             sum *= scale;
             asm volatile("" : "+v"(sum));             // (summed by all lanes, not below)
             if (own >= 0) {
                 if constexpr (kBlockSum) {
                     atomicAdd(&s_g[e * kGrad2d + own], sum);
                 } else {
-                    const uint64_t row = *reinterpret_cast<const uint64_t*>(
-                        reinterpret_cast<const char*>(s_e[3]) + at);
-                    atomicAdd(reinterpret_cast<float*>(mine + row), sum);
+                    atomicAdd(reinterpret_cast<float*>(mine + s_row[e]), sum);
                 }
             }
         };
-        // from the last to the first, the entries that some pixel of this
-        // wavefront blended in the forward: the blend bits, one word per 64
-        // entries (the batch starts at a multiple of 64 entries of the tile's
-        // list).  Without usable bits (a forward with another work split has
-        // another wavefront partition) every entry is visited; each pixel
-        // still decides its own.  Entries at or past this wavefront's last
-        // blend change nothing.
-        const int wcnt = min(cnt, max(0, int(wend) - lo));
-        const uint64_t chunk = (start >> 6) + uint64_t(tile) + uint64_t(lo / 64);
-        for (int c = ((wcnt - 1) >> 6) << 6; c >= 0; c -= 64) {
-            uint64_t m = use_bits ? uint64_t(wbits[chunk + uint64_t(c >> 6)]) : ~uint64_t(0);
-            if (wcnt - c < 64) m &= (uint64_t(1) << (wcnt - c)) - 1;
-            const int q = c + lane;
-            const uint64_t other = m & ~__ballot(q < cnt && s_plain[q] != 0u);
-            while (m != 0) {
-                const int hb = 63 - __builtin_clzll(m);
-                m ^= uint64_t(1) << hb;
-                entry(c + hb, ((other >> hb) & 1u) == 0);
+        // two entries (kListed).  The splat's constants go to the sums, which
+        // cancels less and costs nothing here: the kernel waits for its chain of
+        // entries, not for instructions.
+        auto pair = [&](const EntryPair& g) {
+            float ab[2], dx[2], dy[2];
+            uint64_t clamped[2];
+            uint32_t row[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                float t, alpha;
+                uint64_t hit;
+                const float p2 = splat_exponent(g.a[u], g.b[u], X[0], Y[0], dx[u], dy[u], t);
+                splat_test<1>(g.b[u].y, false, &p2, &alpha, &hit, clamped + u);
+                const uint32_t pos = uint32_t(lo) + (g.at[u] >> 4);
+                hit &= __ballot(pos < last[0]);
+                ab[u] = lane_of(hit) ? alpha : 0.0f;
+                row[u] = g.at[u] >> 4;
+            }
+            float sum[2], gv[2][kGrad2d];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const float4 b = g.b[u], c = g.c[u];
+                const float T0 = Ts[0] * __builtin_amdgcn_rcpf(1.0f - ab[u]);
+                const float w = ab[u] * T0;
+                const float diff = fmaf(g2[0], c.x, fmaf(g1[0], b.w, g0[0] * b.z)) - Sb[0];
+                float dp = ab[u] * (T0 * diff);
+                Sb[0] = fmaf(ab[u], diff, Sb[0]);
+                Ts[0] = T0;
+                dp = lane_of(clamped[u]) ? 0.0f : dp;
+                lane_moments<S>(&dp, dx + u, dy + u, gv[u]);
+                gv[u][5] *= c.w;
+                gv[u][6] = w * g0[0];
+                gv[u][7] = w * g1[0];
+                gv[u][8] = w * g2[0];
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) sum[u] = wave_sum9(gv[u]);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                // lanes 0 and 8 hold Sx and Sy: exchange them (rotation by 8
+                // within a row of 16 lanes)
+                const float cross = g.a[u].w * dpp_f<kDppRowRor8>(sum[u]);
+                sum[u] = own == 0 ? fmaf(g.c[u].y, sum[u], cross) : sum[u];
+                sum[u] = own == 1 ? fmaf(g.c[u].z, sum[u], cross) : sum[u];
+                sum[u] *= scale;
+                asm volatile("" : "+v"(sum[u]));      // (summed by all lanes, not below)
+            }
+            if (own >= 0) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    if constexpr (kBlockSum) {
+                        atomicAdd(&s_g[row[u] * kGrad2d + uint32_t(own)], sum[u]);
+                    } else if (row[u] != uint32_t(BATCH)) {
+                        atomicAdd(reinterpret_cast<float*>(mine + s_row[row[u]]), sum[u]);
+                    }
+                }
+            }
+        };
+        if constexpr (kListed) {
+            // the entries the blend bits name (below), from the last to the
+            // first: their LDS offsets, then the entry of zeros
+            const int wcnt = min(cnt, max(0, int(wend) - lo));
+            uint64_t word = ~uint64_t(0);             // lane l: the bits of entries [64 l, 64 l + 64)
+            if (use_bits && lane * 64 < wcnt)
+                word = wbits[(start >> 6) + uint64_t(tile) + uint64_t(lo / 64 + lane)];
+            uint32_t n = 0;
+#pragma unroll
+            for (int c = BATCH - 64; c >= 0; c -= 64) {
+                uint64_t m = uint64_t(uint32_t(__builtin_amdgcn_readlane(int(word), c / 64))) |
+                             uint64_t(uint32_t(__builtin_amdgcn_readlane(int(word >> 32), c / 64))) << 32;
+                if (!use_bits) {                      // as the forward would have left them
+                    m = 0;
+                    for (int e = c; e < min(c + 64, wcnt); ++e) {
+                        float dx, dy, t, alpha;
+                        uint64_t hit, clamped;
+                        const float p2 = splat_exponent(s_e[0][e], s_e[1][e], X[0], Y[0], dx, dy, t);
+                        splat_test<1>(s_e[1][e].y, false, &p2, &alpha, &hit, &clamped);
+                        hit &= __ballot(uint32_t(lo + e) < last[0]);
+                        m |= hit != 0 ? uint64_t(1) << (e - c) : 0;
+                    }
+                }
+                if (wcnt - c < 64) m = wcnt > c ? m & ((uint64_t(1) << (wcnt - c)) - 1) : 0;
+                const uint32_t all = uint32_t(__builtin_popcountll(m));
+                if ((m >> lane) & 1u)
+                    s_list[wave][n + all - 1u - lanes_below(m)] = uint16_t((c + lane) * 16);
+                n += all;
+            }
+            if (lane < kListPad) s_list[wave][n + uint32_t(lane)] = uint16_t(BATCH * 16);
+            wave_lds_sync();
+            for (uint32_t b0 = 0; b0 < n; b0 += 64) {
+                const uint32_t nb = min(64u, n - b0);
+                const uint32_t at = s_list[wave][b0 + uint32_t(lane)];
+                EntryPair g0, g1;
+                g0.load<true>(s_e, at, 0);
+                for (uint32_t i = 0; i < nb; i += kListStep) {
+                    g1.load<true>(s_e, at, i + 2);
+                    pair(g0);
+                    g0.load<true>(s_e, at, (i + kListStep) & 63u);
+                    pair(g1);
+                }
+            }
+        } else {
+            // from the last to the first, the entries that some pixel of this
+            // wavefront blended in the forward: the blend bits, one word per 64
+            // entries (the batch starts at a multiple of 64 entries of the tile's
+            // list).  Without usable bits (a forward with another work split has
+            // another wavefront partition) every entry is visited; each pixel
+            // still decides its own.  Entries at or past this wavefront's last
+            // blend change nothing.
+            const int wcnt = min(cnt, max(0, int(wend) - lo));
+            const uint64_t chunk = (start >> 6) + uint64_t(tile) + uint64_t(lo / 64);
+            for (int c = ((wcnt - 1) >> 6) << 6; c >= 0; c -= 64) {
+                uint64_t m = use_bits ? uint64_t(wbits[chunk + uint64_t(c >> 6)]) : ~uint64_t(0);
+                if (wcnt - c < 64) m &= (uint64_t(1) << (wcnt - c)) - 1;
+                const int q = c + lane;
+                const uint64_t other = m & ~__ballot(q < cnt && s_plain[q] != 0u);
+                while (m != 0) {
+                    const int hb = 63 - __builtin_clzll(m);
+                    m ^= uint64_t(1) << hb;
+                    entry(c + hb, ((other >> hb) & 1u) == 0);
+                }
             }
         }
         if constexpr (kBlockSum) {
@@ -722,7 +943,7 @@ raster_bwd_kernel(RasterViews vt) {
                 const float g = s_g[q];
                 if (g != 0.0f)
                     atomicAdd(reinterpret_cast<float*>(reinterpret_cast<char*>(rv.g2d) +
-                                                       *reinterpret_cast<const uint64_t*>(&s_e[3][q / kGrad2d])) +
+                                                       s_row[q / kGrad2d]) +
                                   q % kGrad2d, g);
             }
         }

@@ -56,3 +56,33 @@ def test_both_sides_of_the_splat_rules(kind, tile, ppt):
     want = obw.raster_backward(rec, vals, ranges, g["grid"], dL, bg=bg)
     for c, nm in enumerate(("u", "v", "A", "B", "C", "opacity", "r", "g", "b")):
         grad_close(got[:, c], want[:, c], name=f"{kind} T={tile} P={ppt} d{nm}")
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 63, 64, 65, 68, 127, 129, 255, 256, 257, 300, 513])
+@pytest.mark.parametrize("kind", ["all", "some", "stops"])
+def test_listed_walk_at_the_edges_of_pairs_words_and_rounds(kind, n):
+    """With one pixel a lane a wavefront lists the entries it visits and takes
+    them in pairs, four at a time; with four it scans their bits one by one.
+    The arithmetic of a pixel is the same, so the forward's outputs are equal
+    bit by bit, for every number of entries around a pair, a word of 64 and a
+    round; the backward's sums differ in their order (the gradient bar), also
+    where it is given the bits of the other split."""
+    sc, cam = scenes.small_scene(43, n, 24, 20, sh_degree=0)
+    sc.scales[:] = sc.scales * np.float32(0.3 if kind == "some" else 40.0)
+    sc.opacities[:] = np.float32(0.5 if kind == "stops" else 0.015)
+    tgt = scenes.target_image(cam.width, cam.height, 77)
+    want = run_gpu(sc, cam, 1, 0, 0, 16, (0.1, 0.2, 0.3), target=tgt, pixels_per_thread=4)
+    for batch in (64, 128, 256):
+        say(f"[gpu] {kind} n={n} B={batch}")
+        g = run_gpu(sc, cam, 1, 0, 0, 16, (0.1, 0.2, 0.3), target=tgt, pixels_per_thread=1,
+                    lds_batch=batch)
+        for k in ("image", "t_final", "last_contrib", "n_eval", "n_blend"):
+            assert torch.equal(g[k], want[k]), (batch, k)
+        grad_close(g["grad2d"], want["grad2d"], name=f"{kind} n={n} B={batch}")
+        view = g["_view"]
+        view.opt.pixels_per_thread = view.opt_sync.pixels_per_thread = 4
+        view.forward(g["_dev"], g["_image"])
+        view.opt.pixels_per_thread = 1
+        view.raster_bwd(g["dL"].cuda())
+        torch.cuda.synchronize()
+        grad_close(view.grad2d().cpu(), want["grad2d"], name=f"{kind} n={n} B={batch} other bits")
