@@ -218,7 +218,6 @@ tgs::PrepView prep_view(const tgs_camera& cam, const tgs::Grid& grid, uint8_t* w
     v.touched = reinterpret_cast<uint32_t*>(ws + L.tiles_touched);
     v.rects = reinterpret_cast<uint2*>(ws + L.rects);
     v.depth_key = reinterpret_cast<uint32_t*>(ws + L.depth_key[0]);
-    v.depth_val = reinterpret_cast<uint32_t*>(ws + L.depth_val[0]);
     v.g2d = reinterpret_cast<const float*>(ws + L.grad2d);
     v.nonfinite = reinterpret_cast<uint32_t*>(ws + L.nonfinite);
     return v;
@@ -284,7 +283,7 @@ tgs_status enqueue_counts(uint8_t* ws, const tgs::Layout& L, const tgs::Grid& gr
     // out, their number stays on the device
     uint32_t* dkeys[2] = {u32(L.depth_key[0]), u32(L.depth_key[1])};
     uint32_t* dvals[2] = {u32(L.depth_val[0]), u32(L.depth_val[1])};
-    TGS_HIP(tgs::radix_sort(dkeys, dvals, uint64_t(n), 32, u32(L.sort_counts), partials, dres, strm,
+    TGS_HIP(tgs::radix_sort(dkeys, dvals, uint64_t(n), 32, u32(L.sort_counts), false, dres, strm,
                             true, 0xFFFFFFFFu));
     const uint32_t* kept = u32(L.sort_counts) + tgs::radix_kept_offset(uint64_t(n));
     *order = dvals[*dres];

@@ -148,7 +148,6 @@ struct PrepView {
     uint32_t* touched;        // forward out / backward in
     uint2* rects;             // forward out: packed tile rectangle (pack_rect)
     uint32_t* depth_key;      // forward out
-    uint32_t* depth_val;      // forward out
     const float* g2d;         // backward in
     uint32_t* nonfinite;      // forward out: count of Gaussians culled for non-finite input
     float* pos_out;           // backward, optional: this view's positional statistic
@@ -177,14 +176,16 @@ hipError_t launch_preprocess_bwd(const tgs_gaussians& g, const PrepViews& views,
                                  const tgs_grads& out, float* pos_stat, float* col_stat,
                                  uint8_t* visible, hipStream_t s);
 
-// Stable LSD radix sort of (key, value) uint32 pairs on bits [0, bits).
-// Returns the index (0 or 1) of the buffer pair holding the result.  With
+// Stable LSD radix sort of uint32 keys on bits [0, bits), with their input
+// positions as values (written to vals; vals[0] need not hold anything).
+// Returns the index (0 or 1) of the buffer pair holding the result; the sorted
+// keys are there only with keys_out (keys[0] may be overwritten).  With
 // drop_on, the pairs whose key equals drop are left out; the number of pairs
 // kept is then counts[radix_kept_offset(count)] on the device (the result
 // holds that many).  counts needs radix_counts_elems(count) entries.
 int radix_sort_passes(int bits);
 hipError_t radix_sort(uint32_t* const keys[2], uint32_t* const vals[2], uint64_t count, int bits,
-                      uint32_t* counts, uint64_t* partials, int* result, hipStream_t s,
+                      uint32_t* counts, bool keys_out, int* result, hipStream_t s,
                       bool drop_on = false, uint32_t drop = 0u);
 uint64_t radix_counts_elems(uint64_t count);
 uint64_t radix_kept_offset(uint64_t count);

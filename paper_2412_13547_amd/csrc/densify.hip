@@ -21,7 +21,7 @@ __global__ void __launch_bounds__(256)
 densify_score_kernel(int64_t n, const float* __restrict__ pos, const float* __restrict__ col,
                      const int32_t* __restrict__ count, float tau_pos, float tau_col, int color,
                      uint8_t* __restrict__ selected, uint32_t* __restrict__ keys,
-                     uint32_t* __restrict__ vals, uint32_t* __restrict__ n_candidates) {
+                     uint32_t* __restrict__ n_candidates) {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     bool cand = false;
     if (i < n) {
@@ -40,10 +40,7 @@ densify_score_kernel(int64_t n, const float* __restrict__ pos, const float* __re
             }
         }
         selected[i] = cand ? 1 : 0;
-        if (keys) {
-            keys[i] = cand ? ~__float_as_uint(score) : kNotSelected;
-            vals[i] = uint32_t(i);
-        }
+        if (keys) keys[i] = cand ? ~__float_as_uint(score) : kNotSelected;
     }
     const uint64_t b = __ballot(cand);
     if (__lane_id() == 0 && b) atomicAdd(n_candidates, uint32_t(__popcll(b)));
@@ -78,7 +75,7 @@ uint64_t densify_workspace_bytes(int64_t n) {
 hipError_t launch_densify(int64_t n, const float* pos, const float* col, const int32_t* count,
                           float tau_pos, float tau_col, int color, int64_t budget,
                           uint8_t* selected, uint32_t* n_selected, uint8_t* ws, hipStream_t s) {
-    // workspace: [candidate count | pad] keys[2] vals[2] radix counts, scan partials
+    // workspace: [candidate count | pad] keys[2] vals[2] radix counts
     auto* n_cand = reinterpret_cast<uint32_t*>(ws);
     const uint64_t un = uint64_t(n);
     uint8_t* p = ws + 256;
@@ -91,8 +88,6 @@ hipError_t launch_densify(int64_t n, const float* pos, const float* col, const i
         p += align_up(un * 4, 256);
     }
     auto* counts = reinterpret_cast<uint32_t*>(p);
-    p += align_up(radix_counts_elems(un) * 4, 256);
-    auto* partials = reinterpret_cast<uint64_t*>(p);
     hipError_t e = fill_u32(n_cand, 0u, 1, s);
     if (e != hipSuccess) return e;
     const bool capped = budget >= 0;
@@ -100,7 +95,7 @@ hipError_t launch_densify(int64_t n, const float* pos, const float* col, const i
     if (n > 0) {
         densify_score_kernel<<<blocks, 256, 0, s>>>(n, pos, col, count, tau_pos, tau_col, color,
                                                     selected, capped ? keys[0] : nullptr,
-                                                    capped ? vals[0] : nullptr, n_cand);
+                                                    n_cand);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (!capped || n == 0) {
@@ -108,7 +103,7 @@ hipError_t launch_densify(int64_t n, const float* pos, const float* col, const i
         return hipGetLastError();
     }
     int res = 0;
-    if ((e = radix_sort(keys, vals, un, 32, counts, partials, &res, s)) != hipSuccess) return e;
+    if ((e = radix_sort(keys, vals, un, 32, counts, true, &res, s)) != hipSuccess) return e;
     densify_budget_kernel<<<blocks, 256, 0, s>>>(n, keys[res], vals[res], uint64_t(budget), n_cand,
                                                  selected, n_selected);
     return hipGetLastError();

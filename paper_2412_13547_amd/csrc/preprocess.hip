@@ -285,7 +285,6 @@ __global__ void __launch_bounds__(256) preprocess_fwd_kernel(tgs_gaussians g, Pr
         pv.touched[i] = nt;
         pv.rects[i] = rect;
         pv.depth_key[i] = nt > 0 ? __float_as_uint(r[2].y) : 0xFFFFFFFFu;
-        pv.depth_val[i] = uint32_t(i);
     }
 }
 

@@ -1,5 +1,5 @@
-// Device-wide primitives: exclusive scan and stable LSD radix sort of
-// (uint32 key, uint32 value) pairs, written for wave64.
+// Device-wide primitives: exclusive scan and stable LSD radix sort of uint32
+// keys with their input positions as values, written for wave64.
 //
 // Radix sort over 8-bit digits, least significant first: two set-up
 // launches, then one launch per digit (a decoupled look-back over the tiles
@@ -8,19 +8,28 @@
 //      counts the digits of all passes over its share of the keys (eight
 //      LDS copies), adds its counts to the totals and clears part of the
 //      look-back states.
-//   2. sort_pass, per digit: a block takes the next tile of 4096 keys in
-//      launch order (a ticket, so that every earlier tile's block has
+//   2. sort_pass, per digit: a block takes the next tile of 4096 or 8192 keys
+//      in launch order (a ticket, so that every earlier tile's block has
 //      started) and each digit's first output slot from a prefix over the
 //      totals (the first pass's first tile also stores the number of pairs
-//      kept).  It ranks the tile's keys among those of their digit, 1024 at
-//      a time in input order (equal digits inside a wavefront ranked with
-//      eight ballots, wavefronts ordered by a prefix over them per digit,
-//      so equal keys keep their input order), publishes its count per digit
-//      at once, sums the counts of the earlier tiles per digit by reading
-//      their published states from the nearest back (a state that already
-//      holds an inclusive prefix ends the walk) and publishes its own
-//      inclusive prefix, while the other wavefronts order the tile by digit
-//      in LDS; then it writes each digit's run to consecutive output slots.
+//      kept).  A wavefront ranks its keys, 256 or 512 in a row, among those
+//      of their digit: equal digits of 64 keys with eight ballots, its counts
+//      so far in its own LDS words, so without a barrier; a prefix over the
+//      wavefronts per digit follows, so equal keys keep their input order.
+//      The block publishes its count per digit at once, sums the counts of the
+//      earlier tiles per digit by reading their published states from the
+//      nearest back (a state that already holds an inclusive prefix ends the
+//      walk) and publishes its own inclusive prefix, while the other
+//      wavefronts order the tile by digit in LDS; then it writes each digit's
+//      run to consecutive output slots.  The first pass makes the positions,
+//      the last one leaves the keys out unless they are asked for.
+// Up to 8192 keys are sorted by one block in one launch (sort_small).
+//
+// What bounds it: with few tiles a pass is a chain of latencies (ticket, keys,
+// ranks, look-back, run), of which three barriers per 1024 keys were half; with
+// many, the rate of its blocks.  Four passes 104 -> 80 us at 3M keys (a pass
+// moves 48 MB: 10 us at the copy rate), 47 -> 35 at 200K, 39 -> 27 at 20K; all
+// launches 41 -> 12 us at 2K keys.
 // A published state is one word, flag << 30 | count, so a reader needs no
 // ordering beyond the word itself; waits are bounded.
 // The sort may drop every pair whose key equals a given value (it is
@@ -115,7 +124,7 @@ template <typename T, int NT, bool SAT = false>
 __device__ __forceinline__ T block_exclusive_scan(T x, T& total);
 
 constexpr int kScatterThreads = 1024;
-constexpr int kScatterRounds = kSortTile / kScatterThreads;
+constexpr int kScatterWaves = kScatterThreads / 64;
 
 constexpr int kLookbackWindow = 4;                   // states read at once
 
@@ -154,90 +163,133 @@ __device__ __forceinline__ uint32_t look_back(const uint32_t* states, uint32_t t
     return sum;
 }
 
+// Ranks a wavefront's IT x 64 keys (in input order: round, lane) among its own
+// keys of their digit; cnt (256 words of the wavefront's own, zeros) ends as its
+// count per digit.  Equal digits of a round are found with eight ballots.  No
+// barrier: LDS operations of a wavefront take effect in order.
+template <int IT>
+__device__ __forceinline__ void rank_keys(const uint32_t* key, uint32_t ok, int shift,
+                                          uint16_t* cnt, uint32_t* rk) {
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        const uint64_t valid = __ballot((ok >> it) & 1u);
+        uint32_t lo = uint32_t(valid), hi = uint32_t(valid >> 32);
+#pragma unroll
+        for (int b = 0; b < kRadixBits; ++b) {
+            const uint32_t x = uint32_t(__builtin_amdgcn_sbfe(int(key[it]), uint32_t(shift + b), 1u));
+            const uint64_t m = __ballot(x != 0u);
+            lo &= ~(uint32_t(m) ^ x);
+            hi &= ~(uint32_t(m >> 32) ^ x);
+        }
+        const uint64_t peers = uint64_t(hi) << 32 | lo;
+        rk[it] = uint32_t(__popcll(peers)) << 8 |
+                 __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        uint32_t d = (key[it] >> shift) & (kRadixBuckets - 1);
+        const uint32_t before = cnt[d], rank = rk[it] & 0xFFu, peers = rk[it] >> 8;
+        rk[it] = before + rank;
+        __builtin_amdgcn_wave_barrier();
+        if (((ok >> it) & 1u) != 0u && rank == 0u) cnt[d] = uint16_t(before + peers);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// After a barrier: the wavefronts' counts of digit tid (tid < 256) into first
+// ranks per wavefront; returns the count over all of them.
+__device__ __forceinline__ uint32_t fold_counts(uint16_t (*cnt)[kRadixBuckets], int tid) {
+    uint32_t c[kScatterWaves], acc = 0;
+#pragma unroll
+    for (int w = 0; w < kScatterWaves; ++w) c[w] = cnt[w][tid];
+#pragma unroll
+    for (int w = 0; w < kScatterWaves; ++w) {
+        cnt[w][tid] = uint16_t(acc);
+        acc += c[w];
+    }
+    return acc;
+}
+
+// Exclusive scan over the first 256 threads (four wavefronts; the others pass
+// through its barrier).  s_w: four words.
+__device__ __forceinline__ uint32_t scan_digits(uint32_t x, uint32_t* s_w, uint32_t& total) {
+    const int tid = threadIdx.x;
+    uint32_t excl = 0, sum = 0;
+    if (tid < kRadixBuckets) {
+        excl = wave_exclusive_sum(x, sum);
+        if ((tid & 63) == 0) s_w[tid >> 6] = sum;
+    }
+    __syncthreads();
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < kRadixBuckets / 64; ++w) {
+        if (w < (tid >> 6)) excl += s_w[w];
+        total += s_w[w];
+    }
+    return excl;
+}
+
+template <int IT>
 __global__ void __launch_bounds__(kScatterThreads)
 sort_pass(const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in,
           uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out, PassInput in,
           int pass, SortArea area, uint32_t tiles) {
-    constexpr int W = kScatterThreads / 64;
-    __shared__ uint32_t s_key[kSortTile], s_val[kSortTile];   // the tile, ordered by digit
-    __shared__ uint32_t run[kRadixBuckets];       // keys of the digit ranked so far
-    __shared__ uint32_t lstart[kRadixBuckets];    // first local slot per digit
-    __shared__ uint32_t gbase[kRadixBuckets];     // first output slot per digit
-    // per round: (round + 1) << 16 | count of the digit in the wavefront,
-    // written by the digit's first lane; then the wavefront's first rank
-    __shared__ uint32_t wcnt[W][kRadixBuckets];
-    __shared__ uint32_t s_tile;
+    constexpr int kTile = kScatterThreads * IT;
+    __shared__ uint32_t s_key[kTile], s_val[kTile];   // the tile, ordered by digit
+    __shared__ uint32_t lstart[kRadixBuckets];        // first local slot per digit
+    __shared__ uint32_t gofs[kRadixBuckets];          // output slot less local slot
+    __shared__ uint16_t cnt[kScatterWaves][kRadixBuckets];
+    __shared__ uint32_t s_w[2][4], s_tile;
     const int tid = threadIdx.x, wave = tid >> 6;
     const int shift = pass * kRadixBits;
     if (tid == 0) s_tile = atomicAdd(&area.tickets[pass], 1u);
-    if (tid < kRadixBuckets) run[tid] = 0u;
-    for (int j = tid; j < W * kRadixBuckets; j += kScatterThreads) (&wcnt[0][0])[j] = 0u;
-    __syncthreads();
+    uint32_t dtotal = tid < kRadixBuckets ? area.total[pass * kRadixBuckets + tid] : 0u;
+    for (int j = int(lane_id()); j < kRadixBuckets; j += 64) cnt[wave][j] = 0;
+    // the digits' first output slots: a prefix over the pass's totals (its
+    // barrier also hands out the ticket)
+    uint32_t all;
+    const uint32_t first = scan_digits(dtotal, s_w[0], all);
     const uint32_t tile = s_tile;
     if (tile >= tiles) return;                                   // (more blocks than tiles)
     uint32_t* states = area.states + uint64_t(pass) * tiles * kRadixBuckets;
     uint32_t* mine = states + uint64_t(tile) * kRadixBuckets;
     const uint64_t count = in.count();
-    const uint64_t base = uint64_t(tile) * kSortTile;
+    const uint64_t base = uint64_t(tile) * kTile;
+    if (pass == 0 && tile == 0 && tid == 0) *area.kept = all;
     if (base >= count) {                                         // empty tile, block-uniform
         if (tid < kRadixBuckets)
             __hip_atomic_store(mine + tid, kStateIncl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
-    // the tile's keys, all loads in flight at once
-    uint32_t key[kScatterRounds], val[kScatterRounds], rk[kScatterRounds];
+    // the tile's keys, IT x 64 in a row per wavefront, all loads in flight at once
+    const uint32_t left = uint32_t(min(count - base, uint64_t(kTile)));
+    const uint32_t at = uint32_t(wave) * (64 * IT) + lane_id();
+    keys_in += base;
+    if (vals_in) vals_in += base;
+    uint32_t key[IT], val[IT], rk[IT], ok = 0;
 #pragma unroll
-    for (int it = 0; it < kScatterRounds; ++it) {
-        const uint64_t idx = base + uint64_t(it) * kScatterThreads + tid;
-        key[it] = idx < count ? keys_in[idx] : 0u;
-        val[it] = idx < count ? vals_in[idx] : 0u;
+    for (int it = 0; it < IT; ++it) {
+        const uint32_t l = at + uint32_t(it) * 64;
+        key[it] = l < left ? keys_in[l] : 0u;
+        val[it] = vals_in ? (l < left ? vals_in[l] : 0u) : uint32_t(base) + l;
     }
-    // the digits' first output slots: a prefix over the pass's totals
-    uint32_t all;
-    const uint32_t first = block_exclusive_scan<uint32_t, kScatterThreads>(
-        tid < kRadixBuckets ? area.total[pass * kRadixBuckets + tid] : 0u, all);
-    if (tid < kRadixBuckets) gbase[tid] = first;
-    if (pass == 0 && tile == 0 && tid == 0) *area.kept = all;
-    // rank every key among the tile's keys of its digit, in input order
 #pragma unroll
-    for (int it = 0; it < kScatterRounds; ++it) {
-        const uint64_t idx = base + uint64_t(it) * kScatterThreads + tid;
-        const uint32_t k = key[it];
-        const bool valid = idx < count && in.kept(k);
-        const uint32_t d = (k >> shift) & (kRadixBuckets - 1);
-        uint64_t peers = __ballot(valid);
-#pragma unroll
-        for (int b = 0; b < kRadixBits; ++b) {
-            const bool bit = (d >> b) & 1u;
-            const uint64_t m = __ballot(bit);
-            peers &= bit ? m : ~m;
-        }
-        const uint32_t rank = __popcll(peers & lanemask_lt());
-        const uint32_t tag = uint32_t(it + 1) << 16;
-        if (valid && rank == 0) wcnt[wave][d] = tag | uint32_t(__popcll(peers));
-        __syncthreads();
-        // per digit: the first rank of every wavefront this round
-        if (tid < kRadixBuckets) {
-            uint32_t acc = run[tid];
-            for (int w = 0; w < W; ++w) {
-                const uint32_t v = wcnt[w][tid];
-                wcnt[w][tid] = acc;                   // < 4096: never carries a tag
-                acc += (v >> 16) == uint32_t(it + 1) ? (v & 0xFFFFu) : 0u;
-            }
-            run[tid] = acc;
-        }
-        __syncthreads();
-        rk[it] = valid ? wcnt[wave][d] + rank : 0u;
-        __syncthreads();                              // wcnt is rewritten next round
-    }
+    for (int it = 0; it < IT; ++it)
+        ok |= at + uint32_t(it) * 64 < left && in.kept(key[it]) ? 1u << it : 0u;
+    rank_keys<IT>(key, ok, shift, cnt[wave], rk);
+    __syncthreads();
     // the tile's count per digit: published at once (the first tile's is
     // already inclusive), and its prefix gives each digit's local slots
-    const uint32_t c = tid < kRadixBuckets ? run[tid] : 0u;
-    if (tid < kRadixBuckets)
+    uint32_t c = 0;
+    if (tid < kRadixBuckets) {
+        c = fold_counts(cnt, tid);
         __hip_atomic_store(mine + tid, (tile == 0 ? kStateIncl : kStateAgg) | c, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
+    }
     uint32_t total;
-    const uint32_t ls = block_exclusive_scan<uint32_t, kScatterThreads>(c, total);
+    const uint32_t ls = scan_digits(c, s_w[1], total);
     if (tid < kRadixBuckets) lstart[tid] = ls;
     __syncthreads();
     // the first four wavefronts sum the earlier tiles' counts per digit and
@@ -248,27 +300,95 @@ sort_pass(const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ val
         if (tile > 0)
             __hip_atomic_store(mine + tid, kStateIncl | (before + c), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
-        gbase[tid] += before;
+        gofs[tid] = first + before - ls;
     }
 #pragma unroll
-    for (int it = 0; it < kScatterRounds; ++it) {
-        const uint64_t idx = base + uint64_t(it) * kScatterThreads + tid;
-        const uint32_t k = key[it];
-        if (idx < count && in.kept(k)) {
-            const uint32_t pos = lstart[(k >> shift) & (kRadixBuckets - 1)] + rk[it];
-            s_key[pos] = k;
+    for (int it = 0; it < IT; ++it) {
+        asm("" : "+v"(key[it]));                      // (its digit is not kept in a register)
+        if ((ok >> it) & 1u) {
+            const uint32_t d = (key[it] >> shift) & (kRadixBuckets - 1);
+            const uint32_t pos = lstart[d] + cnt[wave][d] + rk[it];
+            s_key[pos] = key[it];
             s_val[pos] = val[it];
         }
     }
     __syncthreads();
     // out in local order: a digit's keys go to consecutive output slots, so
     // neighbouring threads write neighbouring addresses
-    for (uint32_t j = tid; j < total; j += kScatterThreads) {
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        const uint32_t j = uint32_t(it * kScatterThreads + tid);
+        if (j >= total) break;
         const uint32_t k = s_key[j];
-        const uint32_t d = (k >> shift) & (kRadixBuckets - 1);
-        const uint32_t pos = gbase[d] + (j - lstart[d]);
-        keys_out[pos] = k;
+        const uint32_t pos = gofs[(k >> shift) & (kRadixBuckets - 1)] + j;
+        if (keys_out) keys_out[pos] = k;
         vals_out[pos] = s_val[j];
+    }
+}
+
+// Few keys: the whole sort in one block, the keys and their 16-bit positions in
+// LDS between the passes (in registers otherwise).
+template <int IT>
+__global__ void __launch_bounds__(kScatterThreads)
+sort_small(uint32_t* __restrict__ keys, uint32_t* __restrict__ vals, uint32_t count, int passes,
+           bool drop_on, uint32_t drop, SortArea area, bool keys_out) {
+    __shared__ uint32_t s_key[kScatterThreads * IT];
+    __shared__ uint16_t s_val[kScatterThreads * IT];
+    __shared__ uint32_t lstart[kRadixBuckets];
+    __shared__ uint16_t cnt[kScatterWaves][kRadixBuckets];
+    __shared__ uint32_t s_w[4];
+    const int tid = threadIdx.x, wave = tid >> 6;
+    const uint32_t at = uint32_t(wave) * (64 * IT) + lane_id();
+    uint32_t key[IT], val[IT], rk[IT], ok = 0, m = 0;
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        val[it] = at + uint32_t(it) * 64;
+        key[it] = val[it] < count ? keys[val[it]] : 0u;
+    }
+#pragma unroll
+    for (int it = 0; it < IT; ++it)
+        ok |= val[it] < count && !(drop_on && key[it] == drop) ? 1u << it : 0u;
+    for (int p = 0; p < passes; ++p) {
+        const int shift = p * kRadixBits;
+        for (int j = int(lane_id()); j < kRadixBuckets; j += 64) cnt[wave][j] = 0;
+        rank_keys<IT>(key, ok, shift, cnt[wave], rk);
+        __syncthreads();
+        const uint32_t ls = scan_digits(tid < kRadixBuckets ? fold_counts(cnt, tid) : 0u, s_w, m);
+        if (tid < kRadixBuckets) lstart[tid] = ls;
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            asm("" : "+v"(key[it]));
+            if ((ok >> it) & 1u) {
+                const uint32_t d = (key[it] >> shift) & (kRadixBuckets - 1);
+                const uint32_t pos = lstart[d] + cnt[wave][d] + rk[it];
+                s_key[pos] = key[it];
+                s_val[pos] = uint16_t(val[it]);
+            }
+        }
+        __syncthreads();
+        ok = 0;
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const uint32_t j = at + uint32_t(it) * 64;
+            if (j < m) {
+                key[it] = s_key[j];
+                val[it] = s_val[j];
+                ok |= 1u << it;
+            }
+        }
+    }
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        if ((ok >> it) & 1u) {
+            const uint32_t j = at + uint32_t(it) * 64;
+            if (keys_out) keys[j] = key[it];
+            vals[j] = val[it];
+        }
+    }
+    if (tid == 0) {
+        *area.kept = m;
+        area.total[kAreaHead - 2] = area.total[kAreaHead - 1] = 0u;
     }
 }
 
@@ -455,18 +575,35 @@ hipError_t exclusive_scan_u32(const uint32_t* in, uint32_t* out, uint64_t count,
                                               reinterpret_cast<uint32_t*>(partials), write_total, s);
 }
 
+template <int IT>
+hipError_t launch_small(uint32_t* keys, uint32_t* vals, uint32_t count, int passes, bool drop_on,
+                        uint32_t drop, const SortArea& area, bool keys_out, hipStream_t s) {
+    sort_small<IT><<<1, kScatterThreads, 0, s>>>(
+        keys, vals, count, passes, drop_on, drop, area, keys_out);
+    return hipGetLastError();
+}
+
 hipError_t radix_sort(uint32_t* const keys[2], uint32_t* const vals[2], uint64_t count, int bits,
-                      uint32_t* counts, uint64_t* partials, int* result, hipStream_t s,
-                      bool drop_on, uint32_t drop) {
-    (void)partials;
-    int cur = 0;
+                      uint32_t* counts, bool keys_out, int* result, hipStream_t s, bool drop_on,
+                      uint32_t drop) {
     const SortArea area = sort_area(counts);
-    if (count == 0) {
-        *result = 0;
-        return fill_u32(area.total, 0u, kAreaHead, s);
-    }
-    const uint64_t tiles = (count + kSortTile - 1) / kSortTile;
     const int passes = std::min(radix_sort_passes(bits), kMaxPasses);
+    *result = 0;
+    if (count == 0) return fill_u32(area.total, 0u, kAreaHead, s);
+    // one block: 12 us up to 4096 keys and 24 up to 8192, six launches take 30 (and
+    // twice 8192 keys no longer fit a block's registers)
+    if (count <= 8 * kScatterThreads) {
+        const uint32_t n = uint32_t(count);
+        if (n <= 4 * kScatterThreads)
+            return launch_small<4>(keys[0], vals[0], n, passes, drop_on, drop, area, keys_out, s);
+        return launch_small<8>(keys[0], vals[0], n, passes, drop_on, drop, area, keys_out, s);
+    }
+    // Tiles of 4096 keys as long as all are resident, two blocks to each of the
+    // 256 CUs (1M keys: 13.4 us a pass, 15.1 with tiles of 8192; 2.05M: both
+    // 18.4); beyond, 8192, one block to a CU (3M: 20 us, 29 with 4096)
+    const bool wide = count > 512 * uint64_t(kSortTile);
+    const uint64_t tile = wide ? 2 * kSortTile : kSortTile;
+    const uint64_t tiles = (count + tile - 1) / tile;
     const uint64_t state_words = uint64_t(passes) * tiles * kRadixBuckets;
     const unsigned hblocks =
         unsigned(std::min<uint64_t>(kHistBlocks, std::max<uint64_t>(1, (count + 4095) / 4096)));
@@ -474,11 +611,15 @@ hipError_t radix_sort(uint32_t* const keys[2], uint32_t* const vals[2], uint64_t
     if (e != hipSuccess) return e;
     sort_hist<<<dim3(hblocks), dim3(1024), 0, s>>>(keys[0], count, passes, drop_on, drop, area,
                                                    state_words);
+    int cur = 0;
     for (int p = 0; p < passes; ++p) {
         PassInput in{count, nullptr, drop_on && p == 0, drop};
         if (drop_on && p > 0) in.dcount = area.kept;
-        sort_pass<<<dim3(unsigned(tiles)), dim3(kScatterThreads), 0, s>>>(
-            keys[cur], vals[cur], keys[1 - cur], vals[1 - cur], in, p, area, uint32_t(tiles));
+        const uint32_t* vin = p == 0 ? nullptr : vals[cur];
+        uint32_t* kout = p + 1 < passes || keys_out ? keys[1 - cur] : nullptr;
+        const auto pass = wide ? sort_pass<8> : sort_pass<4>;
+        pass<<<dim3(unsigned(tiles)), dim3(kScatterThreads), 0, s>>>(
+            keys[cur], vin, kout, vals[1 - cur], in, p, area, uint32_t(tiles));
         cur = 1 - cur;
     }
     *result = cur;

@@ -96,3 +96,24 @@ def test_long_chunks_hold_every_gaussian_in_depth_order():
     assert bool((got == want[None]).all())
     starts = torch.arange(1024, dtype=torch.int32, device="cuda") * n
     assert torch.equal(view.ranges(), torch.stack([starts, starts + n], 1))
+
+
+# one block's sort up to 4096 and 8192 keys, tiles of 4096 keys, and of 8192
+# above 512 x 4096; around a wavefront's and a round's keys
+@pytest.mark.parametrize("n", [1, 2, 64, 65, 256, 257, 1023, 1025, 4096, 4097, 8191, 8192, 8193,
+                               12_289, 512 * 4096, 512 * 4096 + 1])
+@pytest.mark.parametrize("ties", [False, True])
+def test_depth_order_is_the_stable_order(n, ties):
+    """The ids of the Gaussians with tiles by depth bits, equal depths by id."""
+    sc, cam = scenes.small_scene(7, n, 96, 80, sh_degree=0)
+    if ties:
+        sc.means[2] = np.round(sc.means[2], 1)
+    say(f"[gpu] depth order n={n} ties={ties}")
+    dev = api.DeviceScene.from_scene(sc)
+    view = api.View(ctx(), n, cam, 1, 0, 0, 16, (0.0, 0.0, 0.0))
+    view.preprocess_fwd(dev)
+    view.bin_sort(dev)
+    z = view.records()[:, 9].contiguous().view(torch.int32).cpu().numpy().view(np.uint32)
+    ids = np.flatnonzero(view.tiles_touched().cpu().numpy())
+    want = ids[np.argsort(z[ids], kind="stable")]
+    assert np.array_equal(view.depth_order().cpu().numpy(), want)
