@@ -624,8 +624,9 @@ hipError_t launch_super_lists(uint8_t* ws, const Layout& L, const uint32_t* orde
     uint32_t* pair_count = u32(L.row_start) + grid.gy;
     const uint64_t nb = super_blocks(n);
     const unsigned scan_blocks = unsigned(nb * uint64_t(q.supers) / kScanBlock + 1);
-    super_scan_reduce<<<dim3(scan_blocks), dim3(kScanNT), 0, s>>>(u32(q.table), n, dcount, q.supers,
-                                                                 u32(q.sums));
+    if (scan_blocks > 1)                                       // (else no tile is before another)
+        super_scan_reduce<<<dim3(scan_blocks), dim3(kScanNT), 0, s>>>(u32(q.table), n, dcount,
+                                                                     q.supers, u32(q.sums));
     super_scan_down<<<dim3(scan_blocks), dim3(kScanNT), 0, s>>>(u32(q.table), n, dcount, q.supers,
                                                                u32(q.sums));
     super_emit_kernel<<<dim3(unsigned(nb + 1)), dim3(kSuperGauss), emit_lds_bytes(q.supers), s>>>(

@@ -86,3 +86,27 @@ def test_listed_walk_at_the_edges_of_pairs_words_and_rounds(kind, n):
         view.raster_bwd(g["dL"].cuda())
         torch.cuda.synchronize()
         grad_close(view.grad2d().cpu(), want["grad2d"], name=f"{kind} n={n} B={batch} other bits")
+
+
+# the last launch handed out in row order, the first with an order, one share
+# and a tile more, three and a tile less, ragged shares of many buckets
+@pytest.mark.parametrize("gx,gy", [(32, 16), (27, 19), (32, 32), (41, 25), (59, 26), (67, 61)])
+def test_every_tile_is_taken_once(gx, gy):
+    """The order of the tiles only decides when each is rendered: from the
+    weights of the forward before, and from its own, every pixel comes out as
+    in row order, and the gradients' sums differ in their order alone."""
+    w, h = 8 * gx - 3, 8 * gy - 1
+    sc, cam = scenes.small_scene(47, 900, w, h, sh_degree=0)
+    sc.scales[:, ::3] *= np.float32(6.0)
+    tgt = torch.as_tensor(scenes.target_image(w, h, 78)).cuda()
+    say(f"[gpu] tile order {gx}x{gy}")
+    first = run_gpu(sc, cam, 1, 0, 0, 8, (0.2, 0.1, 0.0), target=tgt.cpu().numpy())
+    view, dev = first["_view"], first["_dev"]
+    for _ in range(2):
+        image = torch.full(view.image_shape, float("nan"), device="cuda")
+        view.forward(dev, image)
+        dL, _loss = view.l1_grad(image, tgt)
+        view.raster_bwd(dL)
+        torch.cuda.synchronize()
+        assert torch.equal(image.cpu(), first["image"])
+        grad_close(view.grad2d().cpu(), first["grad2d"], name=f"{gx}x{gy}")
