@@ -12,11 +12,12 @@
 //   1. super_count: per block of 512 consecutive Gaussians and per supertile,
 //      how many of them touch it; the pair count.  An exclusive scan over
 //      (supertile, block) gives every block's first entry in every list.
-//   2. super_emit: a Gaussian's rank in a supertile among its block's comes
-//      from one bit per Gaussian and supertile in LDS (set with atomics, so in
-//      any order; read as a prefix of population counts, so stable).  Its
-//      entry there is (id, column mask << 24 | row mask) of the tiles it covers.
-//      One more block cuts the lists into chunks of equal length.
+//   2. super_emit: the block's Gaussians of a supertile, a bit each, are those
+//      that reach its column and its row of supertiles (a ballot for each
+//      column and row, lanes_reaching); the prefix of their population counts
+//      is a stable rank.  A Gaussian's entry in the supertile's list is (id,
+//      column mask << 24 | row mask) of the tiles it covers.  One more block
+//      cuts the lists into chunks of equal length.
 //   3. super_tile_count: per chunk, the entries covering each of the 64 tiles.
 //   4. super_chunk_scan, super_ranges: every chunk's first place in every
 //      tile, every tile's [start, end).
@@ -39,7 +40,7 @@
 namespace tgs {
 namespace {
 
-constexpr int kSuperWords = kSuperGauss / 32;              // mask words per supertile and block
+constexpr int kSuperWaves = kSuperGauss / 64;
 constexpr int kChunkMin = 256;                             // entries of the shortest chunk
 constexpr int kScanNT = 256, kScanPer = 16;                // table scan
 constexpr int kScanBlock = kScanNT * kScanPer;
@@ -89,11 +90,33 @@ __device__ __forceinline__ uint32_t cover_cols(int lo, int hi, int first) {
     return ((0xFFu >> max(lo - first, 0)) & (0xFFu << (8 - min(hi - first, 8)))) << 24;
 }
 
+// Per wavefront and supertile column (then row) the lanes whose rectangle
+// reaches it, [sx + sy][kSuperWaves]: those reaching supertile (x, y) are the
+// intersection of two of these words.  (sx + sy ballots; a bit or a count set
+// by atomics per Gaussian and supertile took as long as its largest rectangle.)
+// The caller's barrier follows.
+__device__ __forceinline__ void lanes_reaching(const SuperRect& q, int sx, int sy, uint64_t* mask) {
+    const int wv = int(threadIdx.x >> 6), lane = __lane_id();
+    auto fill = [&](int lo, int hi, int count, uint64_t* out) {
+        for (int x0 = 0; x0 < count; x0 += 64) {
+            uint64_t mine = 0;
+            const int top = min(64, count - x0);
+            for (int x = 0; x < top; ++x) {
+                const uint64_t m = __ballot(lo <= x0 + x && x0 + x < hi);
+                if (lane == x) mine = m;
+            }
+            if (lane < top) out[(x0 + lane) * kSuperWaves + wv] = mine;
+        }
+    };
+    fill(q.x0, q.x1, sx, mask);
+    fill(q.y0, q.y1, sy, mask + sx * kSuperWaves);
+}
+
 __global__ void __launch_bounds__(kSuperGauss)
 super_count_kernel(const uint2* __restrict__ rects, const uint32_t* __restrict__ order, int64_t n,
-                   const uint32_t* __restrict__ dcount, int sx, int S, uint32_t* __restrict__ table,
+                   const uint32_t* __restrict__ dcount, int sx, int sy, uint32_t* __restrict__ table,
                    uint2* __restrict__ srect, unsigned long long* __restrict__ pairs) {
-    extern __shared__ uint32_t cnt[];
+    extern __shared__ uint64_t mask[];
     __shared__ uint32_t s_w[kSuperGauss / 64];
     const int64_t s = int64_t(blockIdx.x) * kSuperGauss + threadIdx.x;
     const uint32_t id = s < n ? order[s] : 0u;                 // (before m arrives)
@@ -105,16 +128,20 @@ super_count_kernel(const uint2* __restrict__ rects, const uint32_t* __restrict__
         packed = rects[id];
         srect[s] = packed;
     }
-    for (int k = threadIdx.x; k < S; k += kSuperGauss) cnt[k] = 0;
-    __syncthreads();
     const Rect rc = unpack_rect(packed);
-    const SuperRect q = super_rect(rc);
-    for (int y = q.y0; y < q.y1; ++y)
-        for (int x = q.x0; x < q.x1; ++x) atomicAdd(&cnt[y * sx + x], 1u);
+    lanes_reaching(super_rect(rc), sx, sy, mask);
     uint32_t total;                                            // < 2^31: 512 rectangles of < 2^22
     (void)block_scan<kSuperGauss>(uint32_t(rc.xhi - rc.xlo) * uint32_t(rc.yhi - rc.ylo), s_w, total);
     if (threadIdx.x == 0 && total) atomicAdd(pairs, (unsigned long long)(total));
-    for (int k = threadIdx.x; k < S; k += kSuperGauss) table[uint64_t(k) * nb + blockIdx.x] = cnt[k];
+    for (int k = threadIdx.x; k < sx * sy; k += kSuperGauss) {
+        const int y = k / sx, x = k - y * sx;
+        const uint64_t* mx = mask + x * kSuperWaves;
+        const uint64_t* my = mask + (sx + y) * kSuperWaves;
+        uint32_t c = 0;
+#pragma unroll
+        for (int w = 0; w < kSuperWaves; ++w) c += uint32_t(__popcll(mx[w] & my[w]));
+        table[uint64_t(k) * nb + blockIdx.x] = c;
+    }
 }
 
 // Exclusive scan of the table's S * nb words in place (nb known on the
@@ -270,9 +297,9 @@ super_emit_kernel(const uint2* __restrict__ srect, const uint32_t* __restrict__ 
     }
     const uint32_t blk = blockIdx.x - 1;
     if (blk >= nb || !fits) return;                            // block-uniform
-    uint32_t* mask = lds;                                      // [kSuperWords][S]
-    uint32_t* base = lds + kSuperWords * S;                    // [S]
-    uint16_t* pre = reinterpret_cast<uint16_t*>(base + S);     // [kSuperWords][S]
+    uint2* ent = reinterpret_cast<uint2*>(lds);                // [kSuperGauss] rectangles
+    uint32_t* ids = lds + 2 * kSuperGauss;                     // [kSuperGauss]
+    uint64_t* mask = reinterpret_cast<uint64_t*>(ids + kSuperGauss);
     const int64_t s = int64_t(blk) * kSuperGauss + tid;
     uint2 packed = make_uint2(0u, 0u);
     uint32_t id = 0;
@@ -280,33 +307,54 @@ super_emit_kernel(const uint2* __restrict__ srect, const uint32_t* __restrict__ 
         packed = srect[s];
         id = order[s];
     }
-    for (int k = tid; k < kSuperWords * S; k += kSuperGauss) mask[k] = 0u;
+    // a wavefront takes four supertiles at a time, 16 lanes each and 32
+    // Gaussians to a lane (one supertile, 64 lanes and 8 Gaussians, where there
+    // are too few for all wavefronts): the lanes list their Gaussians' entries in
+    // LDS, and all of them write what is listed, an entry each.  Bound by these
+    // instructions; with a thread writing one Gaussian's entries after the other
+    // few lanes had any left after the first and each wrote a line of its own:
+    // 164 -> 88 us at 3M Gaussians on 510 supertiles, 39 -> 36 on 135, 37 -> 23 at
+    // 1M on 240 (3.4 -> 4.1 at 2K on one).
+    static_assert(kSuperWaves == 8, "512 Gaussians are 16 words of 32");
+    __shared__ uint16_t s_item[kSuperWaves][4 * kSuperGauss];
+    __shared__ uint2 s_row[kSuperWaves][4];
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = __lane_id();
+    const int rows = S < 4 * kSuperWaves ? 1 : 4;
+    const int row = rows == 4 ? lane >> 4 : 0, first_g = (rows * lane & 63) * 8;
+    const uint32_t part = rows == 4 ? 0xFFFFFFFFu : 0xFFu;
+    const uint32_t* half = reinterpret_cast<const uint32_t*>(mask) + (first_g >> 5);
+    uint16_t* item = s_item[wv];
+    int k = wv * rows + row;
+    uint32_t base = k < S ? table[uint64_t(k) * nb + blk] : 0u;
+    ent[tid] = packed;
+    ids[tid] = id;
+    lanes_reaching(super_rect(unpack_rect(packed)), sx, S / sx, mask);
     __syncthreads();
-    const Rect rc = unpack_rect(packed);
-    const SuperRect q = super_rect(rc);
-    const int w = tid >> 5;
-    uint32_t* mw = mask + w * S;
-    for (int y = q.y0; y < q.y1; ++y)
-        for (int x = q.x0; x < q.x1; ++x) atomicOr(&mw[y * sx + x], 1u << (tid & 31));
-    __syncthreads();
-    for (int k = tid; k < S; k += kSuperGauss) {
-        base[k] = table[uint64_t(k) * nb + blk];
-        uint32_t run = 0;
-#pragma unroll
-        for (int j = 0; j < kSuperWords; ++j) {
-            pre[j * S + k] = uint16_t(run);
-            run += uint32_t(__popc(mask[j * S + k]));
+    for (int k0 = wv * rows; k0 < S; k0 += rows * kSuperWaves) {
+        const int next = k + rows * kSuperWaves;
+        const uint32_t base_next = next < S ? table[uint64_t(next) * nb + blk] : 0u;
+        const int y = k / sx, x = k - y * sx;
+        uint32_t w = k < S ? half[x * (2 * kSuperWaves)] & half[(sx + y) * (2 * kSuperWaves)] : 0u;
+        w = (w >> (first_g & 31)) & part;
+        uint32_t total;
+        uint32_t at = wave_exclusive_sum(uint32_t(__popc(w)), total);
+        if (first_g == 0) s_row[wv][row] = make_uint2(base - at, uint32_t(y) << 16 | uint32_t(x));
+        const uint32_t tag = uint32_t(row) << 9 | uint32_t(first_g);
+        while (w != 0u) {
+            item[at++] = uint16_t(tag + uint32_t(__builtin_ctz(w)));
+            w &= w - 1u;
         }
-    }
-    __syncthreads();
-    const uint32_t lt = (1u << (tid & 31)) - 1u;
-    for (int y = q.y0; y < q.y1; ++y) {
-        const uint32_t ym = cover_rows(rc.ylo, rc.yhi, 8 * y);
-        for (int x = q.x0; x < q.x1; ++x) {
-            const int k = y * sx + x;
-            const uint32_t rank = uint32_t(pre[w * S + k]) + uint32_t(__popc(mw[k] & lt));
-            list[base[k] + rank] = make_uint2(id, ym | cover_cols(rc.xlo, rc.xhi, 8 * x));
+        wave_sync();
+        for (uint32_t e = uint32_t(lane); e < total; e += 64u) {
+            const uint32_t it = item[e], g = it & (kSuperGauss - 1);
+            const uint2 to = s_row[wv][it >> 9];
+            const Rect rc = unpack_rect(ent[g]);
+            list[to.x + e] = make_uint2(ids[g], cover_rows(rc.ylo, rc.yhi, 8 * int(to.y >> 16)) |
+                                                    cover_cols(rc.xlo, rc.xhi, 8 * int(to.y & 0xFFFFu)));
         }
+        wave_sync();
+        k = next;
+        base = base_next;
     }
 }
 
@@ -561,16 +609,25 @@ super_expand(const uint2* __restrict__ list, const uint4* __restrict__ desc,
         if (lane >= skip[k] && lane < off[k]) (out + line[k])[lane] = pend[k];
 }
 
-size_t emit_lds_bytes(int S) { return size_t(S) * (kSuperWords * 4 + 4 + kSuperWords * 2); }
+size_t mask_lds_bytes(int sx, int sy) { return size_t(sx + sy) * kSuperWaves * 8; }
+
+// (of which the block that cuts the chunks takes two words per supertile)
+size_t emit_lds_bytes(int sx, int sy) {
+    return std::max(kSuperGauss * 12 + mask_lds_bytes(sx, sy), size_t(sx * sy + 1) * 8);
+}
 
 uint64_t super_blocks(int64_t n) { return (uint64_t(n) + kSuperGauss - 1) / kSuperGauss; }
 
 }  // namespace
 
 hipError_t prepare_supertile_kernels() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&super_emit_kernel),
-                               hipFuncAttributeMaxDynamicSharedMemorySize,
-                               int(emit_lds_bytes(kSuperMax)));
+    // (the most for kSuperMax supertiles in a row)
+    auto allow = [](const void* f, size_t bytes) {
+        return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
+    };
+    hipError_t e = allow(reinterpret_cast<const void*>(&super_count_kernel), mask_lds_bytes(kSuperMax, 1));
+    if (e != hipSuccess) return e;
+    return allow(reinterpret_cast<const void*>(&super_emit_kernel), emit_lds_bytes(kSuperMax, 1));
 }
 
 uint64_t super_max_chunks(uint64_t capacity, int supers) {
@@ -608,8 +665,8 @@ hipError_t launch_super_counts(uint8_t* ws, const Layout& L, const uint32_t* ord
     const SuperLayout& q = L.super;
     const unsigned nb = unsigned(super_blocks(n));
     if (nb == 0) return hipSuccess;
-    super_count_kernel<<<dim3(nb), dim3(kSuperGauss), size_t(q.supers) * 4, s>>>(
-        reinterpret_cast<const uint2*>(ws + L.rects), order, n, dcount, q.sx, q.supers,
+    super_count_kernel<<<dim3(nb), dim3(kSuperGauss), mask_lds_bytes(q.sx, q.supers / q.sx), s>>>(
+        reinterpret_cast<const uint2*>(ws + L.rects), order, n, dcount, q.sx, q.supers / q.sx,
         reinterpret_cast<uint32_t*>(ws + q.table), reinterpret_cast<uint2*>(ws + L.srect), pairs);
     return hipGetLastError();
 }
@@ -629,7 +686,7 @@ hipError_t launch_super_lists(uint8_t* ws, const Layout& L, const uint32_t* orde
                                                                      q.supers, u32(q.sums));
     super_scan_down<<<dim3(scan_blocks), dim3(kScanNT), 0, s>>>(u32(q.table), n, dcount, q.supers,
                                                                u32(q.sums));
-    super_emit_kernel<<<dim3(unsigned(nb + 1)), dim3(kSuperGauss), emit_lds_bytes(q.supers), s>>>(
+    super_emit_kernel<<<dim3(unsigned(nb + 1)), dim3(kSuperGauss), emit_lds_bytes(q.sx, q.supers / q.sx), s>>>(
         reinterpret_cast<const uint2*>(ws + L.srect), order, n, dcount, q.sx, q.supers, grid.gy,
         capacity, pairs, u32(q.table), list, u32(q.first), desc, u32(q.nchunks), u32(q.row_total),
         pair_count);
