@@ -123,25 +123,27 @@ __device__ __forceinline__ void wave_lds_sync() {
 
 // One pixel a lane (views of few tiles): a wavefront's time is a chain of
 // entries, so what an entry waits for counts, and there are registers to
-// spare.  The entries it visits are listed in LDS, and it takes them in pairs,
+// spare.  The entries it visits stand in LDS, and it takes them in pairs,
 // without a branch: the constants of one pair are read while the other is
-// blended, and the two entries of a pair fill each other's latencies.  On a
-// wavefront's own a visited entry takes ~230 cycles in the forward and ~480 in
-// the backward; scanning its bits entry by entry, with the reads waited for and
-// the tests under branches, they took 390 and 750.  412 x 274 pixels of
-// 200K Gaussians: forward 94 -> 70 us, backward 140 -> 103; 128 x 128 of 2K:
-// 24.6 -> 18.9 and 39 -> 28; 960 x 540 of 3M (2040 tiles): 100 -> 84 and
-// 158 -> 159.  With two pixels a lane there are more wavefronts than that and
-// the longer code gains nothing (102 -> 102 and 170 -> 187 at 3600 tiles).
+// blended, and the two entries of a pair fill each other's latencies.  A visited
+// entry takes ~230 cycles in the forward and ~480 in the backward; scanning its
+// bits entry by entry, with the reads waited for and the tests under branches,
+// they took 390 and 750.  The forward's wavefronts also work by themselves
+// (raster_fwd_px1_kernel); the backward's share their sums in LDS, so they
+// list their entries of what the block has staged (a backward by wavefronts,
+// adding to grad2d entry by entry: 103 -> 80 us at 468 tiles, but 158 -> 194 at
+// 2040).  412 x 274 pixels of 200K Gaussians (468 tiles): forward 94 -> 55 us,
+// backward 140 -> 103; 128 x 128 of 2K (64): 24.6 -> 17 and 39 -> 28; 960 x 540 of
+// 3M (2040): 100 -> 80 and 158 -> 159.  With two pixels a lane there are more
+// wavefronts than that and the longer code gains nothing (102 -> 102 and
+// 170 -> 187 at 3600 tiles).
 constexpr int kListStep = 4;                           // entries from one look at the pixels to the next
 constexpr int kListPad = 8;                            // entries past the end that a step may read
 struct EntryPair {
     float4 a[2], b[2], c[2];
-    float blue[2];
     uint32_t at[2];                                    // LDS offsets
-    // entries i and i + 1 of the list the lanes hold; CONSTS: all of s_e[2], not
-    // the blue alone
-    template <bool CONSTS, class E>
+    // entries i and i + 1 of the list the lanes hold
+    template <class E>
     __device__ __forceinline__ void load(const E& s_e, uint32_t list, uint32_t i) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
@@ -150,8 +152,7 @@ struct EntryPair {
             asm("" : "+v"(v));
             a[u] = entry_part(s_e[0], v);
             b[u] = entry_part(s_e[1], v);
-            if constexpr (CONSTS) c[u] = entry_part(s_e[2], v);
-            else blue[u] = entry_part(s_e[2], v).x;
+            c[u] = entry_part(s_e[2], v);
         }
     }
 };
@@ -173,8 +174,9 @@ __device__ __forceinline__ bool splat_plain(const float4 ga, const float4 gb) {
 // wavefront: it would be skipped by each pixel anyway (o <= 0 gives NaN or
 // +inf here, and no exponent passes).
 constexpr float kSkipMargin = 1.0f / 64.0f;
+constexpr float kLog2AlphaMin = -7.99435343685885793f;          // log2(1/255)
 __device__ __forceinline__ float skip_threshold(float o) {
-    return log2f(kAlphaMin / o) - kSkipMargin;
+    return kLog2AlphaMin - __builtin_amdgcn_logf(o) - kSkipMargin;
 }
 
 // Launch shape (the work split): a T x T tile is covered by (T/PX) x (T/PY)
@@ -212,31 +214,30 @@ struct WaveRects {
     }
 };
 
-// Bit w set when the splat's exponent may reach thr somewhere on wavefront
-// w's rectangle: the maximum of the (negative definite) quadratic form over
-// the rectangle -- 0 if it holds the centre, else the largest of the four
-// edge maxima -- plus a margin (1/32 in log2 and a relative bound on the
-// rounding of the form's terms) against thr.  A clear bit is a promise that
-// no pixel of the wavefront passes the per-pixel test, so the wavefront
-// skips the entry without evaluating it; a form that is not negative
-// definite sets every bit.
-template <class S>
-__device__ __forceinline__ uint32_t wave_mask(const float4 ga, float qc, float thr,
-                                              const WaveRects<S>& wr) {
-    constexpr int NW = WaveRects<S>::NW;
-    constexpr uint32_t kAll = NW >= 32 ? 0xFFFFFFFFu : (1u << NW) - 1u;
-    const float u = ga.x, v = ga.y, qa = ga.z, qb = ga.w;
-    if (!(qa < 0.0f && qc < 0.0f && 4.0f * qa * qc > qb * qb)) return kAll;
-    const float ka = -qb / (2.0f * qa);      // maximising dx on a line dy = e: ka e
-    const float kc = -qb / (2.0f * qc);      // maximising dy on a line dx = d: kc d
-    auto f = [&](float d, float e) { return fmaf(d, fmaf(qa, d, qb * e), (qc * e) * e); };
-    uint32_t mask = 0;
-#pragma unroll 1
-    for (int w = 0; w < NW; ++w) {
-        const float xa = wr.x0 + float(w % WaveRects<S>::WX) * wr.stepx;
-        const float ya = wr.y0 + float(w / WaveRects<S>::WX) * wr.stepy;
-        const float d0 = u - (xa + wr.spanx), d1 = u - xa;       // d0 <= d1
-        const float e0 = v - (ya + wr.spany), e1 = v - ya;
+// Whether the splat's exponent may reach thr somewhere on the rectangle
+// [xa, xa + spanx] x [ya, ya + spany]: the maximum of the (negative definite)
+// quadratic form over it -- 0 if it holds the centre, else the largest of the
+// four edge maxima -- plus a margin (1/32 in log2 and a relative bound on the
+// rounding of the form's terms) against thr.  False is a promise that no pixel
+// of the rectangle passes the per-pixel test, so its wavefront skips the entry
+// without evaluating it; a form that is not negative definite (`shaped`) may
+// reach anything.
+struct Reach {
+    float ka, kc;            // maximising dx on a line dy = e: ka e; dy on a line dx = d: kc d
+    bool shaped;
+    __device__ Reach(const float4 ga, float qc) {
+        shaped = ga.z < 0.0f && qc < 0.0f && 4.0f * ga.z * qc > ga.w * ga.w;
+        // (the hardware's reciprocals: a maximum is flat, so their last bit moves
+        // it by far less than the margin)
+        ka = -ga.w * __builtin_amdgcn_rcpf(2.0f * ga.z);
+        kc = -ga.w * __builtin_amdgcn_rcpf(2.0f * qc);
+    }
+    __device__ bool operator()(const float4 ga, float qc, float thr, float xa, float ya, float spanx,
+                               float spany) const {
+        const float qa = ga.z, qb = ga.w;
+        const float d0 = ga.x - (xa + spanx), d1 = ga.x - xa;    // d0 <= d1
+        const float e0 = ga.y - (ya + spany), e1 = ga.y - ya;
+        auto f = [&](float d, float e) { return fmaf(d, fmaf(qa, d, qb * e), (qc * e) * e); };
         float m;
         if (d0 <= 0.0f && d1 >= 0.0f && e0 <= 0.0f && e1 >= 0.0f) {
             m = 0.0f;
@@ -249,7 +250,23 @@ __device__ __forceinline__ uint32_t wave_mask(const float4 ga, float qc, float t
             const float mag = fmaf(-qa * dm, dm, fmaf(fabsf(qb) * dm, em, (-qc * em) * em));
             m += 1.0f / 32.0f + 4e-6f * mag;
         }
-        if (m >= thr) mask |= 1u << w;
+        return m >= thr;
+    }
+};
+
+// The wavefronts whose rectangle it may reach, a bit each.
+template <class S>
+__device__ __forceinline__ uint32_t wave_mask(const float4 ga, float qc, float thr,
+                                              const WaveRects<S>& wr) {
+    constexpr int NW = WaveRects<S>::NW;
+    const Reach reach(ga, qc);
+    if (!reach.shaped) return NW >= 32 ? 0xFFFFFFFFu : (1u << NW) - 1u;
+    uint32_t mask = 0;
+#pragma unroll 1
+    for (int w = 0; w < NW; ++w) {
+        const float xa = wr.x0 + float(w % WaveRects<S>::WX) * wr.stepx;
+        const float ya = wr.y0 + float(w / WaveRects<S>::WX) * wr.stepy;
+        if (reach(ga, qc, thr, xa, ya, wr.spanx, wr.spany)) mask |= 1u << w;
     }
     return mask;
 }
@@ -379,12 +396,8 @@ template <int T, int PPT, int BATCH, bool COUNTS>
 __global__ void __launch_bounds__((Shape<T, PPT>::NT)) __attribute__((amdgpu_waves_per_eu(8)))
 raster_fwd_kernel(RasterViews vt) {
     using S = Shape<T, PPT>;
-    constexpr bool kListed = PPT == 1;
     // splat constants ga, gb and blue, at one stride so one address serves all
-    // (kListed: and an entry of zeros, which blends nothing)
-    __shared__ float4 s_e[3][BATCH + kListed];
-    __shared__ uint16_t s_list[kListed ? S::NT / 64 : 1][kListed ? BATCH + 64 : 1];
-    __shared__ uint8_t s_blend[kListed ? S::NT / 64 : 1][kListed ? BATCH : 1];
+    __shared__ float4 s_e[3][BATCH];
     // wavefronts that look at it; bit 31: splat_plain
     __shared__ uint32_t s_m[BATCH];
     int v;
@@ -423,8 +436,6 @@ raster_fwd_kernel(RasterViews vt) {
         for (int k = 0; k < S::NP; ++k) l = l || Ts[k] > 0.0f;
         return l;
     };
-    const int lane = __lane_id();
-    if (kListed && tid < 3) s_e[tid][BATCH] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     uint32_t base = start;
     for (; base < end; base += BATCH) {
         if (__syncthreads_count(live()) == 0) break;
@@ -442,44 +453,6 @@ raster_fwd_kernel(RasterViews vt) {
             s_m[q] = wave_mask<S>(ga, gb.x, thr, wr) | (splat_plain(ga, gb) ? 1u << 31 : 0u);
         }
         __syncthreads();
-        // two entries (kListed), with the arithmetic of the one below: alpha is
-        // 0 where an entry is skipped, so that one comparison with the floor
-        // decides (a live T is at least the floor, a stopped one negative: a
-        // skipped entry keeps either).  `bit` in the result: the first is
-        // blended by some pixel; the bit above it, the second.
-        auto pair = [&](const EntryPair& g, uint64_t bit) {
-            float alpha[2];
-            uint64_t hit[2], clamped;
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                float dx, dy, t;
-                const float p2 = splat_exponent(g.a[u], g.b[u], X[0], Y[0], dx, dy, t);
-                splat_test<1>(g.b[u].y, false, &p2, alpha + u, hit + u, &clamped);
-                alpha[u] = lane_of(hit[u]) ? alpha[u] : 0.0f;
-            }
-            uint64_t blended = 0;
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const uint32_t pos = base - start + (g.at[u] >> 4) + 1;
-                if constexpr (COUNTS) ntest[0] += g.at[u] < BATCH * 16 && Ts[0] > 0.0f ? 1u : 0u;
-                const float w0 = alpha[u] * Ts[0];
-                const float tn = Ts[0] - w0;
-                const bool stops = tn < kTMin;
-                const uint64_t blend = hit[u] & ~__ballot(stops);
-                if constexpr (COUNTS) {
-                    nblend[0] += lane_of(blend) ? 1u : 0u;
-                    neval[0] = stops && Ts[0] > 0.0f ? pos : neval[0];
-                }
-                const float w = stops ? 0.0f : w0;
-                Ts[0] = stops ? -fabsf(Ts[0]) : tn;
-                c0[0] = fmaf(g.b[u].z, w, c0[0]);
-                c1[0] = fmaf(g.b[u].w, w, c1[0]);
-                c2[0] = fmaf(g.blue[u], w, c2[0]);
-                last[0] = lane_of(blend) ? pos : last[0];
-                blended |= blend != 0 ? bit << u : 0;
-            }
-            return blended;
-        };
         // branch-free per entry: a skipped entry adds exactly 0 and leaves T
         // (entries no pixel of the wavefront can reach are not visited).  A
         // stopped pixel's negative T makes every hit stop it again.
@@ -519,48 +492,6 @@ raster_fwd_kernel(RasterViews vt) {
             }
             return any != 0;
         };
-        if constexpr (kListed) {
-            // the entries of the batch whose wavefront mask has this
-            // wavefront's bit (below), in order: their LDS offsets, then the
-            // entry of zeros
-            uint32_t n = 0;
-#pragma unroll
-            for (int c = 0; c < BATCH; c += 64) {
-                const int q = c + lane;
-                const bool sel = q < cnt && ((s_m[q] >> wave) & 1u) != 0u;
-                const uint64_t m = __ballot(sel);
-                if (sel) s_list[wave][n + lanes_below(m)] = uint16_t(q * 16);
-                n += uint32_t(__builtin_popcountll(m));
-                s_blend[wave][q] = 0;
-            }
-            if (lane < kListPad) s_list[wave][n + uint32_t(lane)] = uint16_t(BATCH * 16);
-            wave_lds_sync();
-            bool go = __ballot(live()) != 0;
-            for (uint32_t b0 = 0; b0 < n && go; b0 += 64) {
-                const uint32_t nb = min(64u, n - b0);
-                const uint32_t at = s_list[wave][b0 + uint32_t(lane)];
-                uint64_t bm = 0, bit = 1;
-                EntryPair g0, g1;
-                g0.load<false>(s_e, at, 0);
-                for (uint32_t i = 0; i < nb && go; i += kListStep) {
-                    g1.load<false>(s_e, at, i + 2);
-                    bm |= pair(g0, bit);
-                    g0.load<false>(s_e, at, (i + kListStep) & 63u);
-                    bm |= pair(g1, bit << 2);
-                    bit <<= kListStep;
-                    go = __ballot(live()) != 0;
-                }
-                if ((bm >> lane) & 1u) s_blend[wave][at >> 4] = 1;
-            }
-            wave_lds_sync();
-            for (int c = 0; c < cnt; c += 64) {
-                const uint64_t bm = __ballot(s_blend[wave][c + lane] != 0);
-                if (lane == 0)                       // entry base + c is chunk (base - start + c) / 64
-                    rv.bits[uint64_t(wave) * rv.bits_stride + (start >> 6) + uint64_t(tile) +
-                            (base - start + uint32_t(c)) / 64u] = bm;
-            }
-            continue;
-        }
         // the entries of the batch whose wavefront mask has this wavefront's
         // bit, in order, while some pixel takes entries (looked at every four:
         // entries after every pixel has stopped change nothing): each 64
@@ -612,6 +543,213 @@ raster_fwd_kernel(RasterViews vt) {
             if (rv.n_blend) rv.n_blend[p] = nblend[k];
             if (rv.n_tested) rv.n_tested[p] = ntest[k];
         }
+    }
+}
+
+// The forward with one pixel a lane.  A wavefront works by itself: it looks at
+// 64 entries of the list at a time, a lane each, keeps those that may reach its
+// 8 x 8 pixels in its own part of LDS, and blends what it has kept once that
+// is kFlush entries, in pairs, with the next entries' records on their way.
+// (Wavefronts that stage entries together wait for the slowest of them at
+// every round: 70 us at 468 tiles, 55 without.  6 wavefronts to a SIMD: with 8
+// its registers spill, 63 and 99 us at 468 and 2040 tiles against 56 and 82.)
+constexpr int kFlush = 48, kKept = kFlush + 64 + kListPad, kPending = 8;
+
+template <int T, bool COUNTS>
+__global__ void __launch_bounds__(T * T) __attribute__((amdgpu_waves_per_eu(6)))
+raster_fwd_px1_kernel(RasterViews vt) {
+    using S = Shape<T, 1>;
+    constexpr int NW = S::NT / 64;
+    // per kept entry ga, gb and (blue, 1-based place in the list)
+    __shared__ float4 s_a[NW][kKept], s_b[NW][kKept];
+    __shared__ float2 s_c[NW][kKept];
+    __shared__ uint32_t s_walked[NW];
+    int v;
+    int64_t tile;
+    if (!locate(vt, blockIdx.x, v, tile)) return;                // block-uniform
+    const RasterView& rv = vt.v[v];
+    const Grid& grid = rv.grid;
+    if (rv.order)                                                // heaviest tiles first
+        tile = __builtin_amdgcn_readfirstlane(
+            int(min(rv.order[tile], uint32_t(grid.num_tiles() - 1))));
+    const int tid = threadIdx.x, lane = __lane_id();
+    const int tx = int(tile % grid.gx), ty = int(tile / grid.gx);
+    const int i = tx * T + S::px(tid), j = ty * T + S::py(tid);
+    uint32_t start, end;
+    tile_range(rv, tile, start, end);
+    const uint32_t len = end - start;
+    WaveRects<S> wr;
+    wr.init(grid, tx, ty, T);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const float xa = wr.x0 + float(wave % WaveRects<S>::WX) * wr.stepx;
+    const float ya = wr.y0 + float(wave / WaveRects<S>::WX) * wr.stepy;
+    const float X = float(grid.stride * i + grid.off_x), Y = float(grid.stride * j + grid.off_y);
+    const bool in = i < grid.w_ds && j < grid.h_ds;
+    float Ts = in ? 1.0f : -1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
+    uint32_t last = 0, neval = len, nblend = 0, ntest = 0;
+    float4* const ka = s_a[wave];
+    float4* const kb = s_b[wave];
+    float2* const kc = s_c[wave];
+
+    struct Pair {
+        float4 a[2], b[2];
+        float2 c[2];
+    };
+    auto load = [&](Pair& g, uint32_t e) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            g.a[u] = ka[e + u];
+            g.b[u] = kb[e + u];
+            g.c[u] = kc[e + u];
+        }
+    };
+    // two entries, with the arithmetic of the kernel above: alpha is 0 where an
+    // entry is skipped, so that one comparison with the floor decides (a live T
+    // is at least the floor, a stopped one negative: a skipped entry keeps
+    // either).  `bit` in the result: the first is blended by some pixel; the
+    // bit above it, the second.
+    auto blend_pair = [&](const Pair& g, uint64_t bit) {
+        float alpha[2];
+        uint64_t hit[2], clamped;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            float dx, dy, t;
+            const float p2 = splat_exponent(g.a[u], g.b[u], X, Y, dx, dy, t);
+            splat_test<1>(g.b[u].y, false, &p2, alpha + u, hit + u, &clamped);
+            alpha[u] = lane_of(hit[u]) ? alpha[u] : 0.0f;
+        }
+        uint64_t blended = 0;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const uint32_t pos = __float_as_uint(g.c[u].y);      // 0: an entry of zeros
+            if constexpr (COUNTS) ntest += pos != 0u && Ts > 0.0f ? 1u : 0u;
+            const float w0 = alpha[u] * Ts;
+            const float tn = Ts - w0;
+            const bool stops = tn < kTMin;
+            const uint64_t blend = hit[u] & ~__ballot(stops);
+            if constexpr (COUNTS) {
+                nblend += lane_of(blend) ? 1u : 0u;
+                neval = stops && Ts > 0.0f ? pos : neval;
+            }
+            const float w = stops ? 0.0f : w0;
+            Ts = stops ? -fabsf(Ts) : tn;
+            c0 = fmaf(g.b[u].z, w, c0);
+            c1 = fmaf(g.b[u].w, w, c1);
+            c2 = fmaf(g.c[u].x, w, c2);
+            last = lane_of(blend) ? pos : last;
+            blended |= blend != 0 ? bit << u : 0;
+        }
+        return blended;
+    };
+
+    // records a look ahead, their indices two
+    float4 n0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), n1 = n0;
+    float n2 = 0.0f;
+    uint32_t nid = 0;
+    auto fetch = [&](uint32_t q) {                               // entry q, whose index is nid
+        if (q < len) {
+            const float4* r = rv.rec + 3 * uint64_t(nid);
+            n0 = r[0];
+            n1 = r[1];
+            n2 = r[2].x;
+        }
+        if (q + 64u < len) nid = rv.vals[start + q + 64u];
+    };
+    if (uint32_t(lane) < len) nid = rv.vals[start + uint32_t(lane)];
+    fetch(uint32_t(lane));
+    uint32_t have = 0, pending = 0, at = 0;                      // (uniform)
+    uint64_t picked = 0;                                         // lane p: who kept in the p-th look pending
+    bool go = __ballot(Ts > 0.0f) != 0;
+    while (at < len && go) {
+        const uint32_t q = at + uint32_t(lane);
+        bool keep = false;
+        float4 ga, gb;
+        stage_conic(n0, n1, ga, gb);
+        if (q < len) {
+            const Reach reach(ga, gb.x);
+            keep = !reach.shaped || reach(ga, gb.x, skip_threshold(n1.y), xa, ya, wr.spanx, wr.spany);
+        }
+        const uint64_t m = __ballot(keep);
+        if (keep) {
+            const uint32_t e = have + lanes_below(m);
+            ka[e] = ga;
+            kb[e] = gb;
+            kc[e] = make_float2(n2, __uint_as_float(q + 1u));
+        }
+        fetch(q + 64u);
+        have += uint32_t(__builtin_popcountll(m));
+        picked = uint32_t(lane) == pending ? m : picked;
+        ++pending;
+        at += 64u;
+        if (have < uint32_t(kFlush) && pending < uint32_t(kPending) && at < len) continue;
+        // blend what is kept, looking at every fourth entry whether some pixel
+        // still takes any
+        if (lane < kListPad) {
+            ka[have + lane] = kb[have + lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            kc[have + lane] = make_float2(0.0f, 0.0f);
+        }
+        wave_lds_sync();
+        uint64_t bm[2] = {0, 0};
+#pragma unroll 1
+        for (uint32_t b0 = 0; b0 < have && go; b0 += 64u) {
+            const uint32_t top = min(have, b0 + 64u);
+            uint64_t word = 0, bit = 1;
+            Pair g0, g1;
+            load(g0, b0);
+            for (uint32_t e = b0; e < top && go; e += uint32_t(kListStep)) {
+                load(g1, e + 2u);
+                word |= blend_pair(g0, bit);
+                load(g0, e + uint32_t(kListStep));
+                word |= blend_pair(g1, bit << 2);
+                bit <<= kListStep;
+                go = __ballot(Ts > 0.0f) != 0;
+            }
+            if (b0 == 0) bm[0] = word;
+            else bm[1] = word;
+        }
+        wave_lds_sync();
+        // the looks' blend bits, one word each
+        uint64_t out = 0;
+        uint32_t before = 0;
+        for (uint32_t p = 0; p < pending; ++p) {
+            const uint64_t pm = uint64_t(uint32_t(__builtin_amdgcn_readlane(int(picked), int(p)))) |
+                                uint64_t(uint32_t(__builtin_amdgcn_readlane(int(picked >> 32), int(p)))) << 32;
+            const uint32_t e = before + lanes_below(pm);
+            const uint64_t word = e < 64u ? bm[0] >> e : bm[1] >> (e - 64u);
+            const uint64_t b = __ballot(lane_of(pm) && (word & 1u) != 0);
+            out = uint32_t(lane) == p ? b : out;
+            before += uint32_t(__builtin_popcountll(pm));
+        }
+        if (uint32_t(lane) < pending)
+            rv.bits[uint64_t(wave) * rv.bits_stride + (start >> 6) + uint64_t(tile) + (at / 64u - pending) + lane] = out;
+        have = pending = 0;
+    }
+    // the tile's weight for the schedule: the most any wavefront walked
+    if (lane == 0) s_walked[wave] = min(at, len);
+    __syncthreads();
+    if (tid == 0) {
+        uint32_t walked = 0;
+        for (int w = 0; w < NW; ++w) walked = max(walked, s_walked[w]);
+        if (rv.work) rv.work[tile] = walked;
+        if (blockIdx.x == vt.first_block[v]) *rv.fwd_split = 1u;
+    }
+    if (!in) return;
+    const uint64_t pix = uint64_t(grid.w_ds) * grid.h_ds;
+    const uint64_t p = uint64_t(j) * grid.w_ds + i;
+    const float Tr = fabsf(Ts);
+    if (rv.image) {
+        rv.image[p] = fmaf(Tr, rv.bg[0], c0);
+        rv.image[pix + p] = fmaf(Tr, rv.bg[1], c1);
+        rv.image[2 * pix + p] = fmaf(Tr, rv.bg[2], c2);
+    }
+    rv.ws_tfinal[p] = Tr;
+    rv.ws_last[p] = last;
+    if (rv.t_final) rv.t_final[p] = Tr;
+    if (rv.last_contrib) rv.last_contrib[p] = last;
+    if constexpr (COUNTS) {
+        if (rv.n_eval) rv.n_eval[p] = neval;
+        if (rv.n_blend) rv.n_blend[p] = nblend;
+        if (rv.n_tested) rv.n_tested[p] = ntest;
     }
 }
 
@@ -907,11 +1045,11 @@ raster_bwd_kernel(RasterViews vt) {
                 const uint32_t nb = min(64u, n - b0);
                 const uint32_t at = s_list[wave][b0 + uint32_t(lane)];
                 EntryPair g0, g1;
-                g0.load<true>(s_e, at, 0);
+                g0.load(s_e, at, 0);
                 for (uint32_t i = 0; i < nb; i += kListStep) {
-                    g1.load<true>(s_e, at, i + 2);
+                    g1.load(s_e, at, i + 2);
                     pair(g0);
-                    g0.load<true>(s_e, at, (i + kListStep) & 63u);
+                    g0.load(s_e, at, (i + kListStep) & 63u);
                     pair(g1);
                 }
             }
@@ -1113,6 +1251,9 @@ void launch_both(bool fwd, const RasterViews& vt, hipStream_t s) {
     const dim3 grid(vt.first_block[vt.count]), block(Shape<T, PPT>::NT);
     if (!fwd) {
         raster_bwd_kernel<T, PPT, B><<<grid, block, 0, s>>>(vt);
+    } else if constexpr (PPT == 1) {
+        if (wants_counts(vt)) raster_fwd_px1_kernel<T, true><<<grid, block, 0, s>>>(vt);
+        else raster_fwd_px1_kernel<T, false><<<grid, block, 0, s>>>(vt);
     } else if (wants_counts(vt)) {
         raster_fwd_kernel<T, PPT, B, true><<<grid, block, 0, s>>>(vt);
     } else {
