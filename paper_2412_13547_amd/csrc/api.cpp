@@ -281,10 +281,12 @@ tgs_status enqueue_counts(uint8_t* ws, const tgs::Layout& L, const tgs::Grid& gr
     // the Gaussians with tiles sorted by depth key (stable, so equal keys
     // keep index order); culled and off-grid ones (key 0xFFFFFFFF) are left
     // out, their number stays on the device
-    uint32_t* dkeys[2] = {u32(L.depth_key[0]), u32(L.depth_key[1])};
+    // (through the rectangles' buffer, which is written after, so that the keys
+    // stay for another sort of the same preprocess)
+    uint32_t* dkeys[2] = {u32(L.srect), u32(L.depth_key[1])};
     uint32_t* dvals[2] = {u32(L.depth_val[0]), u32(L.depth_val[1])};
-    TGS_HIP(tgs::radix_sort(dkeys, dvals, uint64_t(n), 32, u32(L.sort_counts), false, dres, strm,
-                            true, 0xFFFFFFFFu));
+    TGS_HIP(tgs::radix_sort(u32(L.depth_key[0]), dkeys, dvals, uint64_t(n), 32, u32(L.sort_counts),
+                            false, dres, strm, true, 0xFFFFFFFFu));
     const uint32_t* kept = u32(L.sort_counts) + tgs::radix_kept_offset(uint64_t(n));
     *order = dvals[*dres];
     *dcount = kept;

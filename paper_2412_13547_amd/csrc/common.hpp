@@ -177,16 +177,16 @@ hipError_t launch_preprocess_bwd(const tgs_gaussians& g, const PrepViews& views,
                                  uint8_t* visible, hipStream_t s);
 
 // Stable LSD radix sort of uint32 keys on bits [0, bits), with their input
-// positions as values (written to vals; vals[0] need not hold anything).
-// Returns the index (0 or 1) of the buffer pair holding the result; the sorted
-// keys are there only with keys_out (keys[0] may be overwritten).  With
+// positions as values.  Returns the index (0 or 1) of the buffer pair holding
+// the result; the sorted keys are there only with keys_out.  The input is left
+// as it is unless it is one of keys.  With
 // drop_on, the pairs whose key equals drop are left out; the number of pairs
 // kept is then counts[radix_kept_offset(count)] on the device (the result
 // holds that many).  counts needs radix_counts_elems(count) entries.
 int radix_sort_passes(int bits);
-hipError_t radix_sort(uint32_t* const keys[2], uint32_t* const vals[2], uint64_t count, int bits,
-                      uint32_t* counts, bool keys_out, int* result, hipStream_t s,
-                      bool drop_on = false, uint32_t drop = 0u);
+hipError_t radix_sort(const uint32_t* input, uint32_t* const keys[2], uint32_t* const vals[2],
+                      uint64_t count, int bits, uint32_t* counts, bool keys_out, int* result,
+                      hipStream_t s, bool drop_on = false, uint32_t drop = 0u);
 uint64_t radix_counts_elems(uint64_t count);
 uint64_t radix_kept_offset(uint64_t count);
 // Offset (uint32 words) in counts of a 64-bit word the sort sets to zero and
@@ -229,7 +229,7 @@ hipError_t prepare_binning_kernels();
 
 // binning in two levels (supertile.hip).  super_layout lays its buffers out
 // from `at` and returns their bytes (0: the grid has too many supertiles).
-// launch_super_counts adds the view's pairs to *pairs (device, zeroed by the
+// launch_super_counts leaves the view's pairs in *pairs (device, zeroed by the
 // depth sort); launch_super_lists writes the pair count, saturated, to
 // row_start[gy], the pairs and the ranges.
 hipError_t prepare_supertile_kernels();

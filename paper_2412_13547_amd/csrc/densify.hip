@@ -103,7 +103,7 @@ hipError_t launch_densify(int64_t n, const float* pos, const float* col, const i
         return hipGetLastError();
     }
     int res = 0;
-    if ((e = radix_sort(keys, vals, un, 32, counts, true, &res, s)) != hipSuccess) return e;
+    if ((e = radix_sort(keys[0], keys, vals, un, 32, counts, true, &res, s)) != hipSuccess) return e;
     densify_budget_kernel<<<blocks, 256, 0, s>>>(n, keys[res], vals[res], uint64_t(budget), n_cand,
                                                  selected, n_selected);
     return hipGetLastError();

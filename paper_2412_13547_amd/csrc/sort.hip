@@ -330,8 +330,8 @@ sort_pass(const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ val
 // LDS between the passes (in registers otherwise).
 template <int IT>
 __global__ void __launch_bounds__(kScatterThreads)
-sort_small(uint32_t* __restrict__ keys, uint32_t* __restrict__ vals, uint32_t count, int passes,
-           bool drop_on, uint32_t drop, SortArea area, bool keys_out) {
+sort_small(const uint32_t* keys, uint32_t* keys_out, uint32_t* __restrict__ vals, uint32_t count,
+           int passes, bool drop_on, uint32_t drop, SortArea area) {
     __shared__ uint32_t s_key[kScatterThreads * IT];
     __shared__ uint16_t s_val[kScatterThreads * IT];
     __shared__ uint32_t lstart[kRadixBuckets];
@@ -382,7 +382,7 @@ sort_small(uint32_t* __restrict__ keys, uint32_t* __restrict__ vals, uint32_t co
     for (int it = 0; it < IT; ++it) {
         if ((ok >> it) & 1u) {
             const uint32_t j = at + uint32_t(it) * 64;
-            if (keys_out) keys[j] = key[it];
+            if (keys_out) keys_out[j] = key[it];
             vals[j] = val[it];
         }
     }
@@ -576,16 +576,17 @@ hipError_t exclusive_scan_u32(const uint32_t* in, uint32_t* out, uint64_t count,
 }
 
 template <int IT>
-hipError_t launch_small(uint32_t* keys, uint32_t* vals, uint32_t count, int passes, bool drop_on,
-                        uint32_t drop, const SortArea& area, bool keys_out, hipStream_t s) {
-    sort_small<IT><<<1, kScatterThreads, 0, s>>>(
-        keys, vals, count, passes, drop_on, drop, area, keys_out);
+hipError_t launch_small(const uint32_t* keys, uint32_t* keys_out, uint32_t* vals, uint32_t count,
+                        int passes, bool drop_on, uint32_t drop, const SortArea& area,
+                        hipStream_t s) {
+    sort_small<IT><<<1, kScatterThreads, 0, s>>>(keys, keys_out, vals, count, passes, drop_on, drop,
+                                                 area);
     return hipGetLastError();
 }
 
-hipError_t radix_sort(uint32_t* const keys[2], uint32_t* const vals[2], uint64_t count, int bits,
-                      uint32_t* counts, bool keys_out, int* result, hipStream_t s, bool drop_on,
-                      uint32_t drop) {
+hipError_t radix_sort(const uint32_t* input, uint32_t* const keys[2], uint32_t* const vals[2],
+                      uint64_t count, int bits, uint32_t* counts, bool keys_out, int* result,
+                      hipStream_t s, bool drop_on, uint32_t drop) {
     const SortArea area = sort_area(counts);
     const int passes = std::min(radix_sort_passes(bits), kMaxPasses);
     *result = 0;
@@ -594,9 +595,10 @@ hipError_t radix_sort(uint32_t* const keys[2], uint32_t* const vals[2], uint64_t
     // twice 8192 keys no longer fit a block's registers)
     if (count <= 8 * kScatterThreads) {
         const uint32_t n = uint32_t(count);
+        uint32_t* out = keys_out ? keys[0] : nullptr;
         if (n <= 4 * kScatterThreads)
-            return launch_small<4>(keys[0], vals[0], n, passes, drop_on, drop, area, keys_out, s);
-        return launch_small<8>(keys[0], vals[0], n, passes, drop_on, drop, area, keys_out, s);
+            return launch_small<4>(input, out, vals[0], n, passes, drop_on, drop, area, s);
+        return launch_small<8>(input, out, vals[0], n, passes, drop_on, drop, area, s);
     }
     // Tiles of 4096 keys as long as all are resident, two blocks to each of the
     // 256 CUs (1M keys: 13.4 us a pass, 15.1 with tiles of 8192; 2.05M: both
@@ -609,7 +611,7 @@ hipError_t radix_sort(uint32_t* const keys[2], uint32_t* const vals[2], uint64_t
         unsigned(std::min<uint64_t>(kHistBlocks, std::max<uint64_t>(1, (count + 4095) / 4096)));
     hipError_t e = fill_u32(area.total, 0u, kAreaHead, s);     // totals, kept, tickets
     if (e != hipSuccess) return e;
-    sort_hist<<<dim3(hblocks), dim3(1024), 0, s>>>(keys[0], count, passes, drop_on, drop, area,
+    sort_hist<<<dim3(hblocks), dim3(1024), 0, s>>>(input, count, passes, drop_on, drop, area,
                                                    state_words);
     int cur = 0;
     for (int p = 0; p < passes; ++p) {
@@ -619,7 +621,7 @@ hipError_t radix_sort(uint32_t* const keys[2], uint32_t* const vals[2], uint64_t
         uint32_t* kout = p + 1 < passes || keys_out ? keys[1 - cur] : nullptr;
         const auto pass = wide ? sort_pass<8> : sort_pass<4>;
         pass<<<dim3(unsigned(tiles)), dim3(kScatterThreads), 0, s>>>(
-            keys[cur], vin, kout, vals[1 - cur], in, p, area, uint32_t(tiles));
+            p == 0 ? input : keys[cur], vin, kout, vals[1 - cur], in, p, area, uint32_t(tiles));
         cur = 1 - cur;
     }
     *result = cur;

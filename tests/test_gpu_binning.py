@@ -117,3 +117,22 @@ def test_depth_order_is_the_stable_order(n, ties):
     ids = np.flatnonzero(view.tiles_touched().cpu().numpy())
     want = ids[np.argsort(z[ids], kind="stable")]
     assert np.array_equal(view.depth_order().cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("n", [300, 4097, 9000])
+def test_binning_again_gives_the_same_lists(n):
+    """A second bin/sort of one preprocess (culled Gaussians included) finds its
+    keys as the first did."""
+    sc, cam = scenes.small_scene(9, n, 96, 80, sh_degree=0)
+    sc.means[2, ::3] = -4.0
+    say(f"[gpu] binning again n={n}")
+    dev = api.DeviceScene.from_scene(sc)
+    view = api.View(ctx(), n, cam, 1, 0, 0, 16, (0.0, 0.0, 0.0))
+    vals, ranges = _lists(view, dev)
+    order = view.depth_order().cpu()
+    assert 0 < len(order) < n
+    for _ in range(2):
+        view.bin_sort(dev)
+        assert torch.equal(view.depth_order().cpu(), order)
+        assert torch.equal(view.pair_vals().cpu().to(torch.int64), vals)
+        assert torch.equal(view.ranges().cpu().to(torch.int64), ranges)
