@@ -714,11 +714,10 @@ tgs_status tgs_raster_bwd(tgs_context* ctx, const tgs_camera* cam, const tgs_dil
     auto strm = static_cast<hipStream_t>(stream);
     tgs::RasterView v = raster_view(grid, *opt, *st, L);
     v.dL = dL_dimage;
-    TGS_HIP(tgs::fill_u32(reinterpret_cast<uint32_t*>(v.g2d), 0u, uint64_t(n) * tgs::kGrad2d, strm));
     tgs::RasterViews t{};
     add_raster_view(t, v);
     const int ppt = ppt_of(*opt, grid.num_tiles());
-    TGS_HIP(tgs::launch_raster_bwd(opt->tile, ppt, lds_batch_of(*opt, ppt), t, strm));
+    TGS_HIP(tgs::launch_raster_bwd(opt->tile, ppt, lds_batch_of(*opt, ppt), t, n, strm));
     return TGS_OK;
 }
 
@@ -987,11 +986,10 @@ tgs_status tgs_batch_raster_bwd(tgs_context* ctx, int64_t n, int32_t views, cons
     for (int v = 0; v < views; ++v) {
         tgs::RasterView rv = raster_view(grids[v], *opt, states[v], Ls[v]);
         rv.dL = io[v].dL_dimage;
-        TGS_HIP(tgs::fill_u32(reinterpret_cast<uint32_t*>(rv.g2d), 0u, uint64_t(n) * tgs::kGrad2d, strm));
         add_raster_view(rt, rv);
     }
     const int ppt = ppt_of(*opt, rt.first_block[rt.count]);
-    TGS_HIP(tgs::launch_raster_bwd(opt->tile, ppt, lds_batch_of(*opt, ppt), rt, strm));
+    TGS_HIP(tgs::launch_raster_bwd(opt->tile, ppt, lds_batch_of(*opt, ppt), rt, n, strm));
     return TGS_OK;
 }
 

@@ -258,7 +258,7 @@ struct RasterView {
     uint32_t* n_blend;        // forward, optional
     uint32_t* n_tested;       // forward, optional: entries evaluated pixel by pixel
     const float* dL;          // backward in
-    float* g2d;               // backward out (accumulated; zero it first)
+    float* g2d;               // backward out (accumulated; launch_raster_bwd clears it)
     uint32_t* work;           // forward out, optional: entries walked per tile
     uint32_t* order;          // backward, optional: the tile of each workgroup, a
                               //   permutation of the tiles written before the walk
@@ -268,11 +268,14 @@ struct RasterView {
     uint32_t* fwd_split;      // forward out / backward in: the work split (pixels per
                               //   thread) the bits were written with
 };
-struct RasterViews {
+template <int N>
+struct RasterTable {
+    static constexpr int kViews = N;
     int count;
-    uint32_t first_block[kMaxViews + 1];   // workgroups of views [0, v): prefix of tile counts
-    RasterView v[kMaxViews];
+    uint32_t first_block[N + 1];           // workgroups of views [0, v): prefix of tile counts
+    RasterView v[N];
 };
+using RasterViews = RasterTable<kMaxViews>;
 static_assert(sizeof(RasterViews) <= 3584, "raster view table too large for kernel arguments");
 
 // Defaults of the launch options of a tile size: splat records per LDS round
@@ -287,7 +290,8 @@ int default_pixels_per_thread(int tile);
 int default_pixels_per_thread(int tile, int64_t tiles);
 hipError_t launch_raster_fwd(int tile, int ppt, int lds_batch, const RasterViews& views,
                              hipStream_t s);
-hipError_t launch_raster_bwd(int tile, int ppt, int lds_batch, const RasterViews& views,
+// Clears every view's grad2d (n Gaussians), then the blend backward.
+hipError_t launch_raster_bwd(int tile, int ppt, int lds_batch, const RasterViews& views, int64_t n,
                              hipStream_t s);
 // L1 loss and gradient of a table of views in one launch (loss may be null).
 struct L1View {
@@ -297,11 +301,14 @@ struct L1View {
     float* dL;
     double* loss;
 };
-struct L1Views {
+template <int N>
+struct L1Table {
+    static constexpr int kViews = N;
     int count;
-    uint32_t first_block[kMaxViews + 1];   // filled by launch_l1_grad
-    L1View v[kMaxViews];
+    uint32_t first_block[N + 1];           // filled by launch_l1_grad
+    L1View v[N];
 };
+using L1Views = L1Table<kMaxViews>;
 static_assert(sizeof(L1Views) <= 3584, "L1 view table too large for kernel arguments");
 hipError_t launch_l1_grad(L1Views& views, hipStream_t s);
 

@@ -590,16 +590,24 @@ void launch_bwd(const tgs_gaussians& g, const PrepViews& views, const tgs_grads&
 
 // The views' non-finite counters to zero before the forward's atomics (one
 // small launch, so a captured step needs no memset node).
-__global__ void zero_nonfinite_kernel(PrepViews views) {
+struct NonfinitePointers {
+    int count;
+    uint32_t* nonfinite[kMaxViews];
+};
+
+__global__ void zero_nonfinite_kernel(NonfinitePointers p) {
     const int v = int(threadIdx.x);
-    if (v < views.count && views.v[v].nonfinite) *views.v[v].nonfinite = 0u;
+    if (v >= p.count || !p.nonfinite[v]) return;
     // a one-view launch writes the backward's Jacobian rows (every launch the flags word)
-    if (v < views.count && views.v[v].nonfinite) *jac_current(views.v[v]) = views.count == 1 ? 1u : 0u;
+    p.nonfinite[v][0] = 0u;
+    p.nonfinite[v][1] = p.count == 1 ? 1u : 0u;                  // (jac_current)
 }
 
 hipError_t launch_preprocess_fwd(const tgs_gaussians& g, const PrepViews& views, hipStream_t s) {
     if (views.count == 0) return hipSuccess;
-    zero_nonfinite_kernel<<<1, 64, 0, s>>>(views);
+    NonfinitePointers p{views.count, {}};
+    for (int v = 0; v < views.count; ++v) p.nonfinite[v] = views.v[v].nonfinite;
+    zero_nonfinite_kernel<<<1, 64, 0, s>>>(p);
     if (g.n == 0) return hipGetLastError();
     if (views.count == 1) launch_fwd<false>(g, views, s);
     else launch_fwd<true>(g, views, s);

@@ -273,11 +273,18 @@ __device__ __forceinline__ uint32_t wave_mask(const float4 ga, float qc, float t
 
 // Which view workgroup b works on, and its index within the view: the
 // views' workgroups are laid out one view after the other (the index is the
-// tile itself unless the view carries a tile order).
-__device__ __forceinline__ bool locate(const RasterViews& vt, uint32_t b, int& v, int64_t& tile) {
-    if (b >= vt.first_block[vt.count]) return false;
+// tile itself unless the view carries a tile order).  A table of one view needs
+// no search: its fields are read at once where the others wait for the index
+// (arguments are read from host memory, ~1 us a dependent read).
+template <class Table>
+__device__ __forceinline__ bool locate(const Table& vt, uint32_t b, int& v, int64_t& tile) {
     v = 0;
-    while (b >= vt.first_block[v + 1]) ++v;
+    if constexpr (Table::kViews == 1) {
+        if (b >= vt.first_block[1]) return false;
+    } else {
+        if (b >= vt.first_block[vt.count]) return false;
+        while (b >= vt.first_block[v + 1]) ++v;
+    }
     tile = int64_t(b - vt.first_block[v]);
     return true;
 }
@@ -555,9 +562,9 @@ raster_fwd_kernel(RasterViews vt) {
 // its registers spill, 63 and 99 us at 468 and 2040 tiles against 56 and 82.)
 constexpr int kFlush = 48, kKept = kFlush + 64 + kListPad, kPending = 8;
 
-template <int T, bool COUNTS>
+template <int T, bool COUNTS, class Table>
 __global__ void __launch_bounds__(T * T) __attribute__((amdgpu_waves_per_eu(6)))
-raster_fwd_px1_kernel(RasterViews vt) {
+raster_fwd_px1_kernel(Table vt) {
     using S = Shape<T, 1>;
     constexpr int NW = S::NT / 64;
     // per kept entry ga, gb and (blue, 1-based place in the list)
@@ -777,9 +784,9 @@ raster_fwd_px1_kernel(RasterViews vt) {
 //   dL/dA = -1/2 sum dp dx^2,  dL/dB = -sum dp dx dy,  dL/dC = -1/2 sum dp dy^2,
 // with dp = dL/dpower, qa2 = 2 qa, qc2 = 2 qc; the constant factors are applied
 // once per wave to the reduced sums.
-template <int T, int PPT, int BATCH>
+template <int T, int PPT, int BATCH, class Table>
 __global__ void __launch_bounds__((Shape<T, PPT>::NT)) __attribute__((amdgpu_waves_per_eu(7)))
-raster_bwd_kernel(RasterViews vt) {
+raster_bwd_kernel(Table vt) {
     using S = Shape<T, PPT>;
     constexpr bool kListed = PPT == 1;
     // splat constants ga, gb and (blue, 2 qa, 2 qc, 1 / o), at one stride so one
@@ -1097,10 +1104,12 @@ raster_bwd_kernel(RasterViews vt) {
 // bounded number of atomics on one address).
 constexpr uint32_t kL1MaxBlocks = 2048;
 
-__global__ void __launch_bounds__(256) l1_grad_kernel(L1Views vt) {
+template <class Table>
+__global__ void __launch_bounds__(256) l1_grad_kernel(Table vt) {
     __shared__ double wsum[4];
     int v = 0;
-    while (v + 1 < vt.count && blockIdx.x >= vt.first_block[v + 1]) ++v;   // block-uniform
+    if constexpr (Table::kViews > 1)
+        while (v + 1 < vt.count && blockIdx.x >= vt.first_block[v + 1]) ++v;   // block-uniform
     const L1View& lv = vt.v[v];
     const Grid& grid = lv.grid;
     const uint32_t lb = blockIdx.x - vt.first_block[v];
@@ -1154,9 +1163,20 @@ __global__ void __launch_bounds__(256) l1_grad_kernel(L1Views vt) {
 
 // The views' losses to zero before the atomics (a fill kernel, so the step
 // stays capturable without memset nodes).
-__global__ void l1_zero_kernel(L1Views vt) {
+struct LossPointers {
+    int count;
+    double* loss[kMaxViews];
+};
+
+__global__ void l1_zero_kernel(LossPointers p) {
     const int v = int(threadIdx.x);
-    if (v < vt.count && vt.v[v].loss) *vt.v[v].loss = 0.0;
+    if (v < p.count && p.loss[v]) *p.loss[v] = 0.0;
+}
+
+// The table of the one view of a larger one.
+template <template <int> class Table, int N>
+Table<1> first_view(const Table<N>& vt) {
+    return Table<1>{1, {vt.first_block[0], vt.first_block[1]}, {vt.v[0]}};
 }
 
 bool wants_counts(const RasterViews& vt) {
@@ -1187,26 +1207,24 @@ __device__ __forceinline__ uint32_t weight_bucket(uint32_t w) {
     return 32u + (e - 5u) * 8u + ((w >> (e - 3u)) & 7u);         // < 248
 }
 
-// A block takes every gridDim.x-th tile, from its blockIdx.x-th, sorts these and
-// hands them every gridDim.x-th place of the order.  The shares are alike, so
+// A block takes every `shares`-th tile, from its share-th, sorts these and
+// hands them every `shares`-th place of the order.  The shares are alike, so
 // the whole is heaviest first but for the differences between them.  (The time
 // is that of the LDS atomics, one a clock where neighbouring tiles share a
 // bucket: in one block 33 us at 32400 tiles and 9 at 8160, with kOrderShare
 // tiles to a block 5 and 5.)
-__global__ void __launch_bounds__(1024) tile_order_kernel(RasterViews vt) {
+__device__ __forceinline__ void order_share(const RasterView& rv, uint32_t share, uint32_t shares) {
     __shared__ uint32_t s_cur[kOrderBuckets];
-    const RasterView& rv = vt.v[blockIdx.y];
-    if (!rv.order || !rv.work) return;                           // block-uniform
     const uint32_t nt = uint32_t(rv.grid.num_tiles());
-    const uint32_t tid = threadIdx.x, step = gridDim.x;
-    if (blockIdx.x >= nt) return;                                // block-uniform
-    const uint32_t mine = (nt - blockIdx.x - 1) / step + 1;
-    const uint32_t* work = rv.work + blockIdx.x;
-    uint32_t* order = rv.order + blockIdx.x;
+    const uint32_t tid = threadIdx.x;
+    if (!rv.order || !rv.work || share >= nt) return;            // block-uniform
+    const uint32_t mine = (nt - share - 1) / shares + 1;
+    const uint32_t* work = rv.work + share;
+    uint32_t* order = rv.order + share;
     for (uint32_t k = tid; k < kOrderBuckets; k += blockDim.x) s_cur[k] = 0;
     __syncthreads();
     for (uint32_t t = tid; t < mine; t += blockDim.x)
-        atomicAdd(&s_cur[weight_bucket(work[uint64_t(t) * step])], 1u);
+        atomicAdd(&s_cur[weight_bucket(work[uint64_t(t) * shares])], 1u);
     __syncthreads();
     // first slot of every bucket, heaviest bucket first: lane l holds
     // buckets 255 - 4l .. 252 - 4l
@@ -1226,9 +1244,31 @@ __global__ void __launch_bounds__(1024) tile_order_kernel(RasterViews vt) {
     }
     __syncthreads();
     for (uint32_t t = tid; t < mine; t += blockDim.x) {
-        const uint32_t pos = atomicAdd(&s_cur[weight_bucket(work[uint64_t(t) * step])], 1u);
-        if (pos < mine) order[uint64_t(pos) * step] = blockIdx.x + t * step;   // (weights changed under us)
+        const uint32_t pos = atomicAdd(&s_cur[weight_bucket(work[uint64_t(t) * shares])], 1u);
+        if (pos < mine) order[uint64_t(pos) * shares] = share + t * shares;   // (weights changed under us)
     }
+}
+
+__global__ void __launch_bounds__(1024) tile_order_kernel(RasterViews vt) {
+    order_share(vt.v[blockIdx.y], blockIdx.x, gridDim.x);
+}
+
+// What the backward needs first, in one launch: the tile order (the first
+// `shares` blocks of a view) and grad2d of n Gaussians to zero (the others).
+constexpr uint32_t kZeroLoop = 4;                                // 16-byte stores per thread
+
+__global__ void __launch_bounds__(1024) bwd_prepare_kernel(RasterViews vt, uint32_t shares, uint64_t words) {
+    const RasterView& rv = vt.v[blockIdx.y];
+    if (blockIdx.x < shares) {
+        order_share(rv, blockIdx.x, shares);
+        return;
+    }
+    const uint64_t n4 = words / 4;
+    uint64_t i = (uint64_t(blockIdx.x - shares) * kZeroLoop) * 1024u + threadIdx.x;
+#pragma unroll
+    for (uint32_t q = 0; q < kZeroLoop; ++q, i += 1024u)
+        if (i < n4) reinterpret_cast<uint4*>(rv.g2d)[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (blockIdx.x == shares && threadIdx.x < words % 4) rv.g2d[4 * n4 + threadIdx.x] = 0.0f;
 }
 
 constexpr int64_t kOrderShare = 512;                             // tiles per block
@@ -1239,21 +1279,27 @@ constexpr int64_t kOrderShare = 512;                             // tiles per bl
 // and 295.
 constexpr uint32_t kOrderMin = 512;
 
-void launch_tile_order(const RasterViews& vt, hipStream_t s) {
+uint32_t order_shares(const RasterViews& vt) {
+    if (vt.first_block[vt.count] <= kOrderMin) return 0;
     int64_t most = 1;
     for (int k = 0; k < vt.count; ++k) most = std::max(most, vt.v[k].grid.num_tiles());
-    const unsigned shares = unsigned((most + kOrderShare - 1) / kOrderShare);
-    tile_order_kernel<<<dim3(shares, unsigned(vt.count)), dim3(1024), 0, s>>>(vt);
+    return uint32_t((most + kOrderShare - 1) / kOrderShare);
 }
 
 template <int T, int PPT, int B>
 void launch_both(bool fwd, const RasterViews& vt, hipStream_t s) {
     const dim3 grid(vt.first_block[vt.count]), block(Shape<T, PPT>::NT);
-    if (!fwd) {
+    if constexpr (PPT == 1) {
+        const bool counts = wants_counts(vt);
+        auto launch = [&](const auto& table) {
+            if (!fwd) raster_bwd_kernel<T, 1, B><<<grid, block, 0, s>>>(table);
+            else if (counts) raster_fwd_px1_kernel<T, true><<<grid, block, 0, s>>>(table);
+            else raster_fwd_px1_kernel<T, false><<<grid, block, 0, s>>>(table);
+        };
+        if (vt.count == 1) launch(first_view(vt));
+        else launch(vt);
+    } else if (!fwd) {
         raster_bwd_kernel<T, PPT, B><<<grid, block, 0, s>>>(vt);
-    } else if constexpr (PPT == 1) {
-        if (wants_counts(vt)) raster_fwd_px1_kernel<T, true><<<grid, block, 0, s>>>(vt);
-        else raster_fwd_px1_kernel<T, false><<<grid, block, 0, s>>>(vt);
     } else if (wants_counts(vt)) {
         raster_fwd_kernel<T, PPT, B, true><<<grid, block, 0, s>>>(vt);
     } else {
@@ -1271,12 +1317,9 @@ void launch_batch(bool fwd, int batch, const RasterViews& vt, hipStream_t s) {
 // Work splits compiled per tile size: T = 8 one pixel per thread (a single
 // wavefront); T = 16 one, two or four; T = 32 two or four.
 hipError_t launch_raster(bool fwd, int tile, int ppt, int batch, RasterViews vt, hipStream_t s) {
-    if (vt.count == 0 || vt.first_block[vt.count] == 0) return hipSuccess;
-    if (vt.first_block[vt.count] > kOrderMin) {
-        launch_tile_order(vt, s);
-    } else {
+    if (vt.first_block[vt.count] == 0) return hipGetLastError();
+    if (vt.first_block[vt.count] <= kOrderMin)
         for (int k = 0; k < vt.count; ++k) vt.v[k].order = nullptr;
-    }
     if (tile == 8) {
         launch_batch<8, 1>(fwd, batch, vt, s);
     } else if (tile == 32) {
@@ -1293,10 +1336,20 @@ hipError_t launch_raster(bool fwd, int tile, int ppt, int batch, RasterViews vt,
 }  // namespace
 
 hipError_t launch_raster_fwd(int tile, int ppt, int batch, const RasterViews& vt, hipStream_t s) {
+    if (vt.count == 0) return hipSuccess;
+    if (const uint32_t shares = order_shares(vt))
+        tile_order_kernel<<<dim3(shares, unsigned(vt.count)), dim3(1024), 0, s>>>(vt);
     return launch_raster(true, tile, ppt, batch, vt, s);
 }
 
-hipError_t launch_raster_bwd(int tile, int ppt, int batch, const RasterViews& vt, hipStream_t s) {
+hipError_t launch_raster_bwd(int tile, int ppt, int batch, const RasterViews& vt, int64_t n,
+                             hipStream_t s) {
+    if (vt.count == 0) return hipSuccess;
+    const uint32_t shares = order_shares(vt);
+    const uint64_t words = uint64_t(n) * kGrad2d, per = 1024u * kZeroLoop;
+    const uint64_t zero = n > 0 ? std::max<uint64_t>(1, (words / 4 + per - 1) / per) : 0;
+    if (shares + zero > 0)
+        bwd_prepare_kernel<<<dim3(unsigned(shares + zero), unsigned(vt.count)), dim3(1024), 0, s>>>(vt, shares, words);
     return launch_raster(false, tile, ppt, batch, vt, s);
 }
 
@@ -1310,8 +1363,11 @@ hipError_t launch_l1_grad(L1Views& vt, hipStream_t s) {
     }
     vt.first_block[vt.count] = blocks;
     if (vt.count == 0) return hipSuccess;
-    l1_zero_kernel<<<1, 64, 0, s>>>(vt);
-    if (blocks > 0) l1_grad_kernel<<<dim3(blocks), dim3(256), 0, s>>>(vt);
+    LossPointers p{vt.count, {}};
+    for (int k = 0; k < vt.count; ++k) p.loss[k] = vt.v[k].loss;
+    l1_zero_kernel<<<1, 64, 0, s>>>(p);
+    if (blocks > 0 && vt.count == 1) l1_grad_kernel<<<dim3(blocks), dim3(256), 0, s>>>(first_view(vt));
+    else if (blocks > 0) l1_grad_kernel<<<dim3(blocks), dim3(256), 0, s>>>(vt);
     return hipGetLastError();
 }
 
