@@ -291,7 +291,7 @@ tgs_status enqueue_counts(uint8_t* ws, const tgs::Layout& L, const tgs::Grid& gr
     *order = dvals[*dres];
     *dcount = kept;
     if (L.super.supers)
-        return launched(tgs::launch_super_counts(ws, L, *order, n, kept, pair_total(ws, L), strm));
+        return launched(tgs::launch_super_counts(ws, L, *order, n, kept, pair_total(ws, L), grid, strm));
     // entries and pairs per (tile row, block of the depth order); scans ->
     // every block's place in every row
     const uint64_t nrow = uint64_t(grid.gy) * tgs::bin_blocks(n);

@@ -64,6 +64,7 @@ struct SuperLayout {
     uint64_t nchunks;          // uint32
     uint64_t row_total;        // uint32[gy], pairs per tile row
     uint64_t tcnt;             // uint32[max_chunks][64], entries per tile, then first place
+    int direct;                // parts of the depth order in the direct binning, 0: not used
 };
 
 // Byte offsets of the sub-buffers of one view's workspace.
@@ -235,7 +236,8 @@ hipError_t prepare_binning_kernels();
 hipError_t prepare_supertile_kernels();
 uint64_t super_layout(SuperLayout& L, uint64_t at, int64_t n, uint64_t cap, const Grid& grid);
 hipError_t launch_super_counts(uint8_t* ws, const Layout& L, const uint32_t* order, int64_t n,
-                               const uint32_t* dcount, unsigned long long* pairs, hipStream_t s);
+                               const uint32_t* dcount, unsigned long long* pairs, const Grid& grid,
+                               hipStream_t s);
 hipError_t launch_super_lists(uint8_t* ws, const Layout& L, const uint32_t* order, int64_t n,
                               const uint32_t* dcount, const unsigned long long* pairs,
                               const Grid& grid, uint32_t capacity, hipStream_t s);

@@ -27,7 +27,7 @@
 //      of its row and appends their ids to the row's eight tiles.
 // The pair count is on the device after 1; above the capacity the later
 // kernels write nothing and the ranges come out empty, so no step waits for
-// the host.  A list entry holds at least one pair, so a list buffer of the
+// the host.  Small views are binned directly instead (direct_kernel).  A list entry holds at least one pair, so a list buffer of the
 // pair capacity always fits.
 //
 // What bounds it: the 4 bytes written per pair in step 5.  The earlier form
@@ -43,6 +43,7 @@ namespace tgs {
 namespace {
 
 constexpr int kSuperWaves = kSuperGauss / 64;
+constexpr int kDirectTiles = 16;                           // tiles (wavefronts) per block of the direct binning
 constexpr int kChunkMin = 256;                             // entries of the shortest chunk
 constexpr int kScanNT = 256, kScanPer = 16;                // table scan
 constexpr int kScanBlock = kScanNT * kScanPer;
@@ -630,6 +631,105 @@ size_t emit_lds_bytes(int sx, int sy) {
     return std::max(kSuperGauss * 12 + mask_lds_bytes(sx, sy), size_t(sx * sy + 1) * 8);
 }
 
+// The direct binning of small views: a wavefront per tile and part of the depth
+// order looks at the part's rectangles, staged in LDS for the block's 16 tiles,
+// and a ballot per 64 of them gives the tile's, in order.  Once to count (a word
+// per tile and part), then, after a scan of these words by one block, once
+// more to write the ids to their places and the ranges.  Small views are bound
+// by their launches: three here where the two levels take seven.
+template <bool EMIT>
+__global__ void __launch_bounds__(1024)
+direct_kernel(const uint2* __restrict__ rects, const uint32_t* __restrict__ order, int64_t n,
+              const uint32_t* __restrict__ dcount, Grid grid, uint32_t capacity, uint32_t* table,
+              uint32_t* __restrict__ ranges, uint32_t* __restrict__ pair_count,
+              uint32_t* __restrict__ out) {
+    __shared__ uint2 s_rect[1024];
+    __shared__ uint32_t s_id[EMIT ? 1024 : 1];
+    const int64_t m = min(n, int64_t(*dcount));
+    const uint32_t tiles = uint32_t(grid.num_tiles()), parts = gridDim.y, part = blockIdx.y;
+    const int64_t per = ((m + parts - 1) / parts + 63) / 64 * 64;
+    const int64_t first = min(m, per * part), last = min(m, first + per);
+    const int tid = int(threadIdx.x), lane = __lane_id();
+    const uint32_t tile = blockIdx.x * uint32_t(kDirectTiles) +
+                          uint32_t(__builtin_amdgcn_readfirstlane(tid >> 6));
+    const bool mine = tile < tiles;                            // (wavefront-uniform)
+    uint32_t at = 0;
+    if constexpr (EMIT) {
+        const uint32_t total = table[tiles * parts];
+        const bool fits = total <= capacity;
+        if (mine && part == 0 && lane == 0) {
+            const uint32_t b = table[tile * parts], e = table[(tile + 1) * parts];
+            ranges[2 * tile] = fits && e > b ? b : 0u;
+            ranges[2 * tile + 1] = fits && e > b ? e : 0u;
+        }
+        if (blockIdx.x == 0 && part == 0 && tid == 0) *pair_count = total;
+        if (!fits) return;                                     // block-uniform
+        at = mine ? table[tile * parts + part] : 0u;
+    }
+    const int tx = int(tile % uint32_t(grid.gx)), ty = int(tile / uint32_t(grid.gx));
+    for (int64_t s0 = first; s0 < last; s0 += 1024) {
+        const int cnt = int(min(int64_t(1024), last - s0));
+        if (s0 != first) __syncthreads();
+        if (tid < cnt) {
+            const uint32_t id = order[s0 + tid];
+            s_rect[tid] = rects[id];
+            if constexpr (EMIT) s_id[tid] = id;
+        }
+        __syncthreads();
+        if (!mine) continue;
+        for (int k = 0; k < cnt; k += 64) {
+            const Rect r = unpack_rect(s_rect[k + lane]);
+            const bool in = k + lane < cnt && tx >= r.xlo && tx < r.xhi && ty >= r.ylo && ty < r.yhi;
+            const uint64_t b = __ballot(in);
+            if constexpr (EMIT)
+                if (in) out[at + prefix_bits(b)] = s_id[k + lane];
+            at += uint32_t(__builtin_popcountll(b));
+        }
+    }
+    if constexpr (!EMIT)
+        if (mine && lane == 0) table[tile * parts + part] = at;
+}
+
+__global__ void __launch_bounds__(1024)
+direct_scan_kernel(uint32_t* __restrict__ table, uint32_t words, unsigned long long* __restrict__ pairs) {
+    constexpr int kPer = 16;
+    __shared__ uint32_t s_w[16];
+    const uint32_t base = threadIdx.x * uint32_t(kPer);
+    uint32_t v[kPer], sum = 0, total;
+    if (base + kPer <= words) {                                // (16-byte aligned)
+#pragma unroll
+        for (int k = 0; k < kPer; k += 4) {
+            const uint4 w = *reinterpret_cast<const uint4*>(table + base + k);
+            v[k] = w.x; v[k + 1] = w.y; v[k + 2] = w.z; v[k + 3] = w.w;
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) v[k] = base + uint32_t(k) < words ? table[base + k] : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) sum += v[k];
+    uint32_t run = block_scan<1024>(sum, s_w, total);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const uint32_t x = v[k];
+        v[k] = run;
+        run += x;
+    }
+    if (base + kPer <= words) {
+#pragma unroll
+        for (int k = 0; k < kPer; k += 4)
+            *reinterpret_cast<uint4*>(table + base + k) = make_uint4(v[k], v[k + 1], v[k + 2], v[k + 3]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < kPer; ++k)
+            if (base + uint32_t(k) < words) table[base + k] = v[k];
+    }
+    if (threadIdx.x == 0) {
+        table[words] = total;
+        *pairs = total;
+    }
+}
+
 uint64_t super_blocks(int64_t n) { return (uint64_t(n) + kSuperGauss - 1) / kSuperGauss; }
 
 }  // namespace
@@ -646,6 +746,22 @@ hipError_t prepare_supertile_kernels() {
 
 uint64_t super_max_chunks(uint64_t capacity, int supers) {
     return std::min<uint64_t>(kChunkTarget, capacity / kChunkMin + 1) + uint64_t(supers);
+}
+
+// Few enough Gaussians and tiles for every tile to look at every Gaussian: the
+// whole bin/sort (us, in two levels against directly) 34.5 / 22.3 at 2K
+// Gaussians and 64 tiles, 49.3 / 36.1 at 5K and 1200, 59.7 / 50.0 at 20K and
+// 920, 61.7 / 60.9 at 30K and 1200 (36 M tests), slower from there (200K and
+// 468: 43 us of kernels against 58).
+constexpr uint64_t kDirectTests = 32'000'000;
+constexpr int64_t kDirectWords = 16 * 1024;                // words the one-block scan takes
+
+int direct_parts(int64_t n, const Grid& grid) {
+    const int64_t tiles = grid.num_tiles();
+    if (n <= 0 || tiles <= 0 || tiles > kDirectWords || uint64_t(n) > kDirectTests / uint64_t(tiles)) return 0;
+    // parts of the depth order: about 512 blocks in all, at least 1024 Gaussians each
+    const int64_t groups = (tiles + kDirectTiles - 1) / kDirectTiles;
+    return int(std::max<int64_t>(1, std::min({512 / groups, kDirectWords / tiles, (n + 1023) / 1024})));
 }
 
 uint64_t super_layout(SuperLayout& L, uint64_t at, int64_t n, uint64_t cap, const Grid& grid) {
@@ -671,12 +787,25 @@ uint64_t super_layout(SuperLayout& L, uint64_t at, int64_t n, uint64_t cap, cons
     L.nchunks = take(4);
     L.row_total = take(uint64_t(grid.gy) * 4);
     L.tcnt = take(L.max_chunks * 256);
+    // (its table begins where the lists do)
+    L.direct = direct_parts(n, grid);
+    if ((uint64_t(L.direct) * uint64_t(grid.num_tiles()) + 1) * 4 > o - at) L.direct = 0;
     return o - at;
 }
 
 hipError_t launch_super_counts(uint8_t* ws, const Layout& L, const uint32_t* order, int64_t n,
-                               const uint32_t* dcount, unsigned long long* pairs, hipStream_t s) {
+                               const uint32_t* dcount, unsigned long long* pairs, const Grid& grid,
+                               hipStream_t s) {
     const SuperLayout& q = L.super;
+    if (q.direct) {
+        const uint32_t tiles = uint32_t(grid.num_tiles()), parts = uint32_t(q.direct);
+        auto* table = reinterpret_cast<uint32_t*>(ws + q.list);
+        direct_kernel<false><<<dim3((tiles + kDirectTiles - 1) / kDirectTiles, parts), dim3(1024), 0, s>>>(
+            reinterpret_cast<const uint2*>(ws + L.rects), order, n, dcount, grid, 0u, table, nullptr,
+            nullptr, nullptr);
+        direct_scan_kernel<<<1, 1024, 0, s>>>(table, tiles * parts, pairs);
+        return hipGetLastError();
+    }
     const unsigned nb = unsigned(super_blocks(n));
     if (nb == 0) return hipSuccess;
     auto u32 = [&](uint64_t off) { return reinterpret_cast<uint32_t*>(ws + off); };
@@ -701,6 +830,13 @@ hipError_t launch_super_lists(uint8_t* ws, const Layout& L, const uint32_t* orde
     auto* list = reinterpret_cast<uint2*>(ws + q.list);
     auto* desc = reinterpret_cast<uint4*>(ws + q.desc);
     uint32_t* pair_count = u32(L.row_start) + grid.gy;
+    if (q.direct) {
+        const uint32_t tiles = uint32_t(grid.num_tiles()), parts = uint32_t(q.direct);
+        direct_kernel<true><<<dim3((tiles + kDirectTiles - 1) / kDirectTiles, parts), dim3(1024), 0, s>>>(
+            reinterpret_cast<const uint2*>(ws + L.rects), order, n, dcount, grid, capacity,
+            u32(q.list), u32(L.ranges), pair_count, u32(L.pair_vals));
+        return hipGetLastError();
+    }
     const uint64_t nb = super_blocks(n);
     super_emit_kernel<<<dim3(unsigned(nb + 1)), dim3(kSuperGauss), emit_lds_bytes(q.sx, q.supers / q.sx), s>>>(
         reinterpret_cast<const uint2*>(ws + L.srect), order, n, dcount, q.sx, q.supers, grid.gy,

@@ -119,6 +119,27 @@ def test_depth_order_is_the_stable_order(n, ties):
     assert np.array_equal(view.depth_order().cpu().numpy(), want)
 
 
+# views of few Gaussians and tiles are binned directly (up to 32 M tests of one
+# against the other): parts of the depth order and their remainders, tiles
+# past a block's 16, the last direct size of 64 tiles and the first of the two
+# levels, and two-level grids with a remainder of tiles in both directions
+@pytest.mark.parametrize("n,w,h,tile", [
+    (1, 8, 8, 8), (1023, 136, 8, 8), (1025, 128, 64, 8), (2049, 129, 127, 8), (5000, 250, 250, 16),
+    (9000, 640, 360, 8), (500_000, 64, 64, 8), (500_001, 64, 64, 8), (40_000, 333, 201, 8),
+])
+def test_pair_lists_around_the_direct_binning(n, w, h, tile):
+    sc, cam = scenes.small_scene(77 + n, n, w, h, sh_degree=0)
+    if n > 100_000:
+        sc.scales[:] = sc.scales * np.float32(0.2)
+    say(f"[gpu] direct binning n={n} {w}x{h} T={tile}")
+    dev = api.DeviceScene.from_scene(sc)
+    view = api.View(ctx(), n, cam, 1, 0, 0, tile, (0.0, 0.0, 0.0))
+    vals, ranges = _lists(view, dev)
+    o = _oracle(view, obn.grid(w, h, 1, 0, 0, tile))
+    assert torch.equal(vals, o["vals"])
+    assert torch.equal(ranges, o["ranges"])
+
+
 @pytest.mark.parametrize("n", [300, 4097, 9000])
 def test_binning_again_gives_the_same_lists(n):
     """A second bin/sort of one preprocess (culled Gaussians included) finds its
