@@ -152,7 +152,8 @@ typedef struct tgs_state {
     uint64_t pair_capacity;      /* in: the capacity passed to tgs_query_sizes           */
     uint64_t pair_count;         /* out: tile-Gaussian pairs of the last bin/sort        */
     uint32_t key_bits;           /* out: tile-id bits sorted                             */
-    uint32_t reserved;
+    uint32_t reserved;           /* out: the tile grid binned for, by which the raster stages
+                                         know a state of another grid                    */
     uint64_t off_records;        /* out: tgs_record[n]                                    */
     uint64_t off_tiles_touched;  /* out: uint32[n], ds tiles each Gaussian overlaps       */
     uint64_t off_depth_order;    /* out: uint32[n]; its first m entries are the ids of the

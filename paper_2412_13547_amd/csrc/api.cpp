@@ -167,9 +167,21 @@ int key_bits_for(int64_t num_tiles) {
     return b;
 }
 
+uint64_t pair_count_offset(const tgs::Layout& L, const tgs::Grid& grid) {
+    return L.row_start + 4 * uint64_t(grid.gy);
+}
+
+// The tile grid a bin/sort leaves in tgs_state::reserved (at most 1024 x 4096 tiles).
+uint32_t grid_tag(const tgs::Grid& grid) { return uint32_t(grid.gx) | uint32_t(grid.gy) << 16; }
+
 // The raster stages read ranges and pair values written by tgs_bin_sort for
 // the same tile grid; refuse a state that was not binned (or was binned for
-// another grid) instead of reading stale indices.  A batched bin leaves the
+// another grid or capacity) instead of reading stale indices: the ranges lie
+// behind every buffer sized by the capacity, the slices or the row tables, the
+// tile weights also behind those sized by the number of tiles, the pair count
+// behind a word per row, and the tag tells the grids that the buffers'
+// alignment does not.  Another phase with the same tile grid passes: the lists
+// do not depend on it.  A batched bin leaves the
 // count on the device (pending), where the kernels check it themselves.
 tgs_status check_binned(const tgs_state* st, const tgs::Layout& L, const tgs::Grid& grid,
                         bool allow_pending) {
@@ -181,14 +193,21 @@ tgs_status check_binned(const tgs_state* st, const tgs::Layout& L, const tgs::Gr
     } else if (st->pair_count > st->pair_capacity)
         return fail(TGS_ERR_CAPACITY, "state holds %llu pairs, capacity %llu",
                     (unsigned long long)st->pair_count, (unsigned long long)st->pair_capacity);
-    if (st->off_pair_vals != L.pair_vals)
+    if (st->off_pair_vals != L.pair_vals || st->off_ranges != L.ranges ||
+        st->off_tile_work != L.tile_work || st->off_pair_count != pair_count_offset(L, grid) ||
+        (st->reserved != 0 && st->reserved != grid_tag(grid)))
         return fail(TGS_ERR_INVALID_ARG, "state offsets do not match its layout");
     return TGS_OK;
 }
 
+void mark_binned(tgs_state* st, const tgs::Grid& grid) {
+    st->key_bits = uint32_t(key_bits_for(grid.num_tiles()));
+    st->reserved = grid_tag(grid);
+}
+
 void publish_offsets(tgs_state* st, const tgs::Layout& L, const tgs::Grid& grid, int64_t n,
                      const uint32_t* depth_order, const uint8_t* ws) {
-    st->off_pair_count = L.row_start + 4 * uint64_t(grid.gy);
+    st->off_pair_count = pair_count_offset(L, grid);
     st->off_records = L.records;
     st->off_tiles_touched = L.tiles_touched;
     st->off_depth_order = uint64_t(reinterpret_cast<const uint8_t*>(depth_order) - ws);
@@ -610,7 +629,7 @@ tgs_status tgs_bin_sort(tgs_context* ctx, const tgs_gaussians* g, const tgs_came
     if ((s = enqueue_emit(ws, L, grid, g->n, order, dcount, slices, uint32_t(st->pair_capacity),
                           strm)) != TGS_OK)
         return s;
-    st->key_bits = uint32_t(key_bits_for(grid.num_tiles()));   // marks the state as binned
+    mark_binned(st, grid);
     return TGS_OK;
 }
 
@@ -898,7 +917,7 @@ tgs_status tgs_batch_bin_sort(tgs_context* ctx, const tgs_gaussians* g, int32_t 
             status = enqueue_emit(ws, Ls[v], grids[v], g->n, order, dcount, max_slices, cap, vs);
         if (status == TGS_OK) publish_offsets(&st, Ls[v], grids[v], g->n, order, ws);
         st.pair_count = TGS_PAIR_COUNT_PENDING;
-        st.key_bits = uint32_t(key_bits_for(grids[v].num_tiles()));
+        mark_binned(&st, grids[v]);
     }
     // join every chain, also after an error, so no stream is left forked
     for (int c = 1; c < chains; ++c) {
