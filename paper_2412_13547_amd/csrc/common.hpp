@@ -231,8 +231,8 @@ hipError_t prepare_binning_kernels();
 // binning in two levels (supertile.hip).  super_layout lays its buffers out
 // from `at` and returns their bytes (0: the grid has too many supertiles).
 // launch_super_counts leaves the view's pairs in *pairs (device, zeroed by the
-// depth sort); launch_super_lists writes the pair count, saturated, to
-// row_start[gy], the pairs and the ranges.
+// depth sort) and, saturated, in row_start[gy]; launch_super_lists writes the
+// pairs and the ranges.
 hipError_t prepare_supertile_kernels();
 uint64_t super_layout(SuperLayout& L, uint64_t at, int64_t n, uint64_t cap, const Grid& grid);
 hipError_t launch_super_counts(uint8_t* ws, const Layout& L, const uint32_t* order, int64_t n,

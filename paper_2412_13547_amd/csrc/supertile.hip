@@ -178,7 +178,7 @@ super_scan_reduce(const uint32_t* __restrict__ table, int64_t n, const uint32_t*
 __global__ void __launch_bounds__(kScanNT)
 super_scan_down(uint32_t* __restrict__ table, int64_t n, const uint32_t* __restrict__ dcount, int S,
                 const uint32_t* __restrict__ sums, const uint32_t* __restrict__ block_pairs,
-                unsigned long long* __restrict__ pairs) {
+                unsigned long long* __restrict__ pairs, uint32_t* __restrict__ pair_count) {
     __shared__ uint32_t s_w[kScanNT / 64];
     if (blockIdx.x == gridDim.x - 1) {                         // one block more: the pair count
         __shared__ unsigned long long s_p[kScanNT / 64];
@@ -188,7 +188,11 @@ super_scan_down(uint32_t* __restrict__ table, int64_t n, const uint32_t* __restr
         for (int o = 32; o > 0; o >>= 1) p += __shfl_xor(p, o);
         if ((threadIdx.x & 63) == 0) s_p[threadIdx.x >> 6] = p;
         __syncthreads();
-        if (threadIdx.x == 0) *pairs = s_p[0] + s_p[1] + s_p[2] + s_p[3];
+        if (threadIdx.x == 0) {
+            p = s_p[0] + s_p[1] + s_p[2] + s_p[3];
+            *pairs = p;
+            *pair_count = uint32_t(min(p, 0xFFFFFFFFull));
+        }
         return;
     }
     const uint32_t count = table_words(n, dcount, S);
@@ -239,11 +243,9 @@ super_scan_down(uint32_t* __restrict__ table, int64_t n, const uint32_t* __restr
 // desc[c] = (supertile, first entry, end entry); first[s] the supertile's
 // first chunk.  One block.
 __device__ void super_setup(const uint32_t* table, uint32_t nb, int S, int gy, bool fits,
-                            unsigned long long pairs, uint32_t* first, uint4* desc,
-                            uint32_t* nchunks, uint32_t* row_total, uint32_t* pair_count,
+                            uint32_t* first, uint4* desc, uint32_t* nchunks, uint32_t* row_total,
                             uint32_t* s_w, uint32_t* lds) {
     const uint32_t tid = threadIdx.x;
-    if (tid == 0) *pair_count = uint32_t(min(pairs, 0xFFFFFFFFull));
     for (int r = int(tid); r < gy; r += kSuperGauss) row_total[r] = 0u;
     constexpr int per = kSuperMax / kSuperGauss;
     uint32_t* s_first = lds;                                   // [S + 1]
@@ -297,17 +299,15 @@ super_emit_kernel(const uint2* __restrict__ srect, const uint32_t* __restrict__ 
                   const uint32_t* __restrict__ dcount, int sx, int S, int gy, uint32_t capacity,
                   const unsigned long long* __restrict__ pairs, const uint32_t* __restrict__ table,
                   uint2* __restrict__ list, uint32_t* __restrict__ first, uint4* __restrict__ desc,
-                  uint32_t* __restrict__ nchunks, uint32_t* __restrict__ row_total,
-                  uint32_t* __restrict__ pair_count) {
+                  uint32_t* __restrict__ nchunks, uint32_t* __restrict__ row_total) {
     extern __shared__ uint32_t lds[];
     __shared__ uint32_t s_w[kSuperGauss / 64];
     const int tid = int(threadIdx.x);
     const int64_t m = min(n, int64_t(*dcount));
     const uint32_t nb = uint32_t((m + kSuperGauss - 1) / kSuperGauss);
-    const unsigned long long P = *pairs;
-    const bool fits = P <= capacity;
+    const bool fits = *pairs <= capacity;
     if (blockIdx.x == 0) {
-        super_setup(table, nb, S, gy, fits && m > 0, P, first, desc, nchunks, row_total, pair_count, s_w, lds);
+        super_setup(table, nb, S, gy, fits && m > 0, first, desc, nchunks, row_total, s_w, lds);
         return;
     }
     const uint32_t blk = blockIdx.x - 1;
@@ -641,8 +641,7 @@ template <bool EMIT>
 __global__ void __launch_bounds__(1024)
 direct_kernel(const uint2* __restrict__ rects, const uint32_t* __restrict__ order, int64_t n,
               const uint32_t* __restrict__ dcount, Grid grid, uint32_t capacity, uint32_t* table,
-              uint32_t* __restrict__ ranges, uint32_t* __restrict__ pair_count,
-              uint32_t* __restrict__ out) {
+              uint32_t* __restrict__ ranges, uint32_t* __restrict__ out) {
     __shared__ uint2 s_rect[1024];
     __shared__ uint32_t s_id[EMIT ? 1024 : 1];
     const int64_t m = min(n, int64_t(*dcount));
@@ -662,7 +661,6 @@ direct_kernel(const uint2* __restrict__ rects, const uint32_t* __restrict__ orde
             ranges[2 * tile] = fits && e > b ? b : 0u;
             ranges[2 * tile + 1] = fits && e > b ? e : 0u;
         }
-        if (blockIdx.x == 0 && part == 0 && tid == 0) *pair_count = total;
         if (!fits) return;                                     // block-uniform
         at = mine ? table[tile * parts + part] : 0u;
     }
@@ -691,7 +689,8 @@ direct_kernel(const uint2* __restrict__ rects, const uint32_t* __restrict__ orde
 }
 
 __global__ void __launch_bounds__(1024)
-direct_scan_kernel(uint32_t* __restrict__ table, uint32_t words, unsigned long long* __restrict__ pairs) {
+direct_scan_kernel(uint32_t* __restrict__ table, uint32_t words, unsigned long long* __restrict__ pairs,
+                   uint32_t* __restrict__ pair_count) {
     constexpr int kPer = 16;
     __shared__ uint32_t s_w[16];
     const uint32_t base = threadIdx.x * uint32_t(kPer);
@@ -727,6 +726,7 @@ direct_scan_kernel(uint32_t* __restrict__ table, uint32_t words, unsigned long l
     if (threadIdx.x == 0) {
         table[words] = total;
         *pairs = total;
+        *pair_count = total;
     }
 }
 
@@ -797,17 +797,18 @@ hipError_t launch_super_counts(uint8_t* ws, const Layout& L, const uint32_t* ord
                                const uint32_t* dcount, unsigned long long* pairs, const Grid& grid,
                                hipStream_t s) {
     const SuperLayout& q = L.super;
+    uint32_t* pair_count = reinterpret_cast<uint32_t*>(ws + L.row_start) + grid.gy;
     if (q.direct) {
         const uint32_t tiles = uint32_t(grid.num_tiles()), parts = uint32_t(q.direct);
         auto* table = reinterpret_cast<uint32_t*>(ws + q.list);
         direct_kernel<false><<<dim3((tiles + kDirectTiles - 1) / kDirectTiles, parts), dim3(1024), 0, s>>>(
             reinterpret_cast<const uint2*>(ws + L.rects), order, n, dcount, grid, 0u, table, nullptr,
-            nullptr, nullptr);
-        direct_scan_kernel<<<1, 1024, 0, s>>>(table, tiles * parts, pairs);
+            nullptr);
+        direct_scan_kernel<<<1, 1024, 0, s>>>(table, tiles * parts, pairs, pair_count);
         return hipGetLastError();
     }
     const unsigned nb = unsigned(super_blocks(n));
-    if (nb == 0) return hipSuccess;
+    if (nb == 0) return fill_u32(pair_count, 0u, 1, s);
     auto u32 = [&](uint64_t off) { return reinterpret_cast<uint32_t*>(ws + off); };
     uint32_t* block_pairs = u32(L.depth_key[1]);               // (the sort is done with it)
     super_count_kernel<<<dim3(nb), dim3(kSuperGauss), mask_lds_bytes(q.sx, q.supers / q.sx), s>>>(
@@ -818,7 +819,7 @@ hipError_t launch_super_counts(uint8_t* ws, const Layout& L, const uint32_t* ord
         super_scan_reduce<<<dim3(scan_blocks), dim3(kScanNT), 0, s>>>(u32(q.table), n, dcount,
                                                                      q.supers, u32(q.sums));
     super_scan_down<<<dim3(scan_blocks + 1), dim3(kScanNT), 0, s>>>(
-        u32(q.table), n, dcount, q.supers, u32(q.sums), block_pairs, pairs);
+        u32(q.table), n, dcount, q.supers, u32(q.sums), block_pairs, pairs, pair_count);
     return hipGetLastError();
 }
 
@@ -829,19 +830,17 @@ hipError_t launch_super_lists(uint8_t* ws, const Layout& L, const uint32_t* orde
     auto u32 = [&](uint64_t off) { return reinterpret_cast<uint32_t*>(ws + off); };
     auto* list = reinterpret_cast<uint2*>(ws + q.list);
     auto* desc = reinterpret_cast<uint4*>(ws + q.desc);
-    uint32_t* pair_count = u32(L.row_start) + grid.gy;
     if (q.direct) {
         const uint32_t tiles = uint32_t(grid.num_tiles()), parts = uint32_t(q.direct);
         direct_kernel<true><<<dim3((tiles + kDirectTiles - 1) / kDirectTiles, parts), dim3(1024), 0, s>>>(
             reinterpret_cast<const uint2*>(ws + L.rects), order, n, dcount, grid, capacity,
-            u32(q.list), u32(L.ranges), pair_count, u32(L.pair_vals));
+            u32(q.list), u32(L.ranges), u32(L.pair_vals));
         return hipGetLastError();
     }
     const uint64_t nb = super_blocks(n);
     super_emit_kernel<<<dim3(unsigned(nb + 1)), dim3(kSuperGauss), emit_lds_bytes(q.sx, q.supers / q.sx), s>>>(
         reinterpret_cast<const uint2*>(ws + L.srect), order, n, dcount, q.sx, q.supers, grid.gy,
-        capacity, pairs, u32(q.table), list, u32(q.first), desc, u32(q.nchunks), u32(q.row_total),
-        pair_count);
+        capacity, pairs, u32(q.table), list, u32(q.first), desc, u32(q.nchunks), u32(q.row_total));
     const unsigned chunks = unsigned(q.max_chunks);
     super_tile_count<<<dim3((chunks + 3) / 4), dim3(256), 0, s>>>(list, desc, u32(q.nchunks),
                                                                  u32(q.tcnt));

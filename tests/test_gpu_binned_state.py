@@ -39,3 +39,34 @@ def test_a_view_moved_to_another_tile_grid_is_refused(sync):
     view.raster_fwd(again)
     torch.cuda.synchronize()
     assert bool(torch.isfinite(again).all())
+
+
+# binned directly, in two levels and by rows
+@pytest.mark.parametrize("n,w,h,tile", [(3000, 320, 200, 16), (9000, 1016, 640, 8), (3000, 2049, 2048, 8)])
+def test_a_synchronous_overflow_leaves_the_needed_count_on_the_device(n, w, h, tile):
+    """The word at off_pair_count is the count that did not fit, not that of the
+    binning before (tgs_bin_sort reads the count back, reports it and stops)."""
+    sc, cam = scenes.small_scene(5, n, w, h, sh_degree=0)
+    say(f"[gpu] synchronous overflow n={n} {w}x{h} T={tile}")
+    dev = api.DeviceScene.from_scene(sc)
+    view = api.View(ctx(), n, cam, tile=tile, pair_capacity=400 * n)
+    view.preprocess_fwd(dev)
+    view.bin_sort(dev)
+    few = view.pair_count()
+    wide = api.DeviceScene.from_scene(sc)
+    wide.scales *= 3.0
+    view.preprocess_fwd(wide)
+    view.bin_sort(wide)
+    need = view.pair_count()
+    assert need > few + 1000
+    view.reserve(few + 64)
+    view.preprocess_fwd(dev)
+    view.bin_sort(dev)
+    word = view._view(view.state.off_pair_count, 1, torch.int32)
+    assert int(word.item()) == few
+    view.preprocess_fwd(wide)
+    with pytest.raises(api.TgsError) as e:
+        view.bin_sort(wide, grow=False)
+    assert e.value.status == api.TGS_ERR_CAPACITY
+    assert int(view.state.pair_count) == need
+    assert int(view._view(view.state.off_pair_count, 1, torch.int32).item()) == need
