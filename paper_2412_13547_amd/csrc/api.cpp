@@ -262,6 +262,7 @@ tgs::RasterView raster_view(const tgs::Grid& grid, const tgs_options& opt, const
     v.bits = reinterpret_cast<unsigned long long*>(ws + L.blend_bits);
     v.bits_stride = tgs::blend_words(st.pair_capacity, grid.num_tiles());
     v.fwd_split = reinterpret_cast<uint32_t*>(ws + L.fwd_split);
+    v.inf_colour = reinterpret_cast<const uint32_t*>(ws + L.nonfinite) + 2;
     return v;
 }
 
@@ -397,7 +398,7 @@ Layout make_layout(int64_t n, uint64_t cap, const Grid& grid) {
     L.tile_order = take(uint64_t(grid.num_tiles()) * 4);
     L.pix_tfinal = take(uint64_t(grid.w_ds) * uint64_t(grid.h_ds) * 4);
     L.pix_last = take(uint64_t(grid.w_ds) * uint64_t(grid.h_ds) * 4);
-    L.nonfinite = take(8);                // the counter, then whether jac is current
+    L.nonfinite = take(12);               // the counter, whether jac is current, infinite colours
     L.fwd_split = take(4);
     L.blend_bits = take(uint64_t(max_tile_waves(grid.tile)) * blend_words(cap, grid.num_tiles()) * 8);
     L.grad2d = take(un * kGrad2d * 4);

@@ -94,12 +94,13 @@ struct Layout {
     uint64_t pix_last;         // uint32[h_ds][w_ds], 1-based index of each pixel's last
                                //   blended list entry (0: none)
     uint64_t fwd_split;        // uint32: pixels per thread of the last forward
-    uint64_t nonfinite;        // uint32: Gaussians the last preprocess culled for a
+    uint64_t nonfinite;        // uint32[3]: Gaussians the last preprocess culled for a
                                //   non-finite parameter (diagnostics)
     uint64_t jac;              // float[kJacWords][n]: d rgb_c / d dir_a at row 3c + a
                                //   (SH degree >= 1), written by a one-view preprocess
-                               //   (the word after nonfinite is 1 when the last one
-                               //   wrote them); row 9 the record's flags | kHasTiles as a
+                               //   (the word after the count is 1 when the last one
+                               //   wrote them, the third when one of its colours is
+                               //   infinite); row 9 the record's flags | kHasTiles as a
                                //   word, written by every preprocess.  It follows
                                //   tiles_touched directly (jac_rows)
     uint64_t blend_bits;       // uint64[max_tile_waves(T)][blend_words(capacity, tiles)]:
@@ -163,6 +164,7 @@ __host__ __device__ inline float* jac_rows(const PrepView& v, int64_t n) {
     return reinterpret_cast<float*>(v.touched + ((n + 63) / 64) * 64);
 }
 __host__ __device__ inline uint32_t* jac_current(const PrepView& v) { return v.nonfinite + 1; }
+__host__ __device__ inline uint32_t* inf_colour(const PrepView& v) { return v.nonfinite + 2; }
 struct PrepViews {
     int count;
     PrepView v[kMaxViews];
@@ -269,6 +271,10 @@ struct RasterView {
     uint64_t bits_stride;
     uint32_t* fwd_split;      // forward out / backward in: the work split (pixels per
                               //   thread) the bits were written with
+    const uint32_t* inf_colour;   // forward in: not 0 where a colour is infinite.  Times a
+                              //   weight of 0 it is not nothing, so whether some pixel
+                              //   still takes entries is looked at after every entry
+                              //   (else every four)
 };
 template <int N>
 struct RasterTable {

@@ -272,6 +272,10 @@ __global__ void __launch_bounds__(256) preprocess_fwd_kernel(tgs_gaussians g, Pr
         float jac[9];
         const uint32_t nt = preprocess_one<DEG, !MULTI>(pv.cam, pv.grid, ok, m, s, q, op, sh, r,
                                                         rect, jac);
+        // (colours are at least 0: their bits compare as they do)
+        if (max(max(__float_as_int(r[1].z), __float_as_int(r[1].w)), __float_as_int(r[2].x)) ==
+            0x7F800000)
+            *inf_colour(pv) = 1u;
         float4* dst = reinterpret_cast<float4*>(pv.rec + i);
         dst[0] = r[0];
         dst[1] = r[1];
@@ -601,6 +605,7 @@ __global__ void zero_nonfinite_kernel(NonfinitePointers p) {
     // a one-view launch writes the backward's Jacobian rows (every launch the flags word)
     p.nonfinite[v][0] = 0u;
     p.nonfinite[v][1] = p.count == 1 ? 1u : 0u;                  // (jac_current)
+    p.nonfinite[v][2] = 0u;                                      // (inf_colour)
 }
 
 hipError_t launch_preprocess_fwd(const tgs_gaussians& g, const PrepViews& views, hipStream_t s) {

@@ -32,6 +32,8 @@
 #include "common.hpp"
 #include "wave.hpp"
 
+#include <type_traits>
+
 namespace tgs {
 namespace {
 
@@ -418,8 +420,10 @@ raster_fwd_kernel(RasterViews vt) {
     const int tid = threadIdx.x;
     const int tx = int(tile % grid.gx), ty = int(tile / grid.gx);
     const int i0 = tx * T + S::px(tid), j0 = ty * T + S::py(tid);
+    const uint32_t inf_colour = *rv.inf_colour;                  // (on its way with the range)
     uint32_t start, end;
     tile_range(rv, tile, start, end);
+    const uint32_t every = __builtin_amdgcn_readfirstlane(int(inf_colour)) == 0 ? 3u : 0u;
     WaveRects<S> wr;
     wr.init(grid, tx, ty, T);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -501,9 +505,10 @@ raster_fwd_kernel(RasterViews vt) {
         };
         // the entries of the batch whose wavefront mask has this wavefront's
         // bit, in order, while some pixel takes entries (looked at every four:
-        // entries after every pixel has stopped change nothing): each 64
-        // entries' bits become one ballot, and the wavefront visits the set
-        // bits only, so an entry its rectangle cannot reach costs nothing.
+        // entries after every pixel has stopped change nothing, as long as the
+        // colours are finite): each 64 entries' bits become one ballot, and the
+        // wavefront visits the set bits only, so an entry its rectangle cannot
+        // reach costs nothing.
         // Per 64 entries it also collects the bits of those some pixel of
         // this wavefront blended: they are all the backward has to visit.
         for (int c = 0; c < cnt; c += 64) {
@@ -517,7 +522,7 @@ raster_fwd_kernel(RasterViews vt) {
                 const int j = int(__builtin_ctzll(m));
                 m &= m - 1;
                 if (entry(c + j, ((other >> j) & 1u) == 0)) bm |= uint64_t(1) << j;
-                if ((u & 3u) == 0u) go = __ballot(live()) != 0;
+                if ((u & every) == 0u) go = __ballot(live()) != 0;
             }
             if (__lane_id() == 0)                    // entry base + c is chunk (base - start + c) / 64
                 rv.bits[uint64_t(wave) * rv.bits_stride + (start >> 6) + uint64_t(tile) +
@@ -582,6 +587,7 @@ raster_fwd_px1_kernel(Table vt) {
     const int tid = threadIdx.x, lane = __lane_id();
     const int tx = int(tile % grid.gx), ty = int(tile / grid.gx);
     const int i = tx * T + S::px(tid), j = ty * T + S::py(tid);
+    const uint32_t inf_colour = *rv.inf_colour;                  // (on its way with the range)
     uint32_t start, end;
     tile_range(rv, tile, start, end);
     const uint32_t len = end - start;
@@ -610,16 +616,17 @@ raster_fwd_px1_kernel(Table vt) {
             g.c[u] = kc[e + u];
         }
     };
-    // two entries, with the arithmetic of the kernel above: alpha is 0 where an
-    // entry is skipped, so that one comparison with the floor decides (a live T
-    // is at least the floor, a stopped one negative: a skipped entry keeps
+    // two entries (or one), with the arithmetic of the kernel above: alpha is 0
+    // where an entry is skipped, so that one comparison with the floor decides (a
+    // live T is at least the floor, a stopped one negative: a skipped entry keeps
     // either).  `bit` in the result: the first is blended by some pixel; the
     // bit above it, the second.
-    auto blend_pair = [&](const Pair& g, uint64_t bit) {
+    auto blend = [&](auto count, const Pair& g, uint64_t bit) {
+        constexpr int U = decltype(count)::value;
         float alpha[2];
         uint64_t hit[2], clamped;
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < U; ++u) {
             float dx, dy, t;
             const float p2 = splat_exponent(g.a[u], g.b[u], X, Y, dx, dy, t);
             splat_test<1>(g.b[u].y, false, &p2, alpha + u, hit + u, &clamped);
@@ -627,7 +634,7 @@ raster_fwd_px1_kernel(Table vt) {
         }
         uint64_t blended = 0;
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < U; ++u) {
             const uint32_t pos = __float_as_uint(g.c[u].y);      // 0: an entry of zeros
             if constexpr (COUNTS) ntest += pos != 0u && Ts > 0.0f ? 1u : 0u;
             const float w0 = alpha[u] * Ts;
@@ -664,6 +671,7 @@ raster_fwd_px1_kernel(Table vt) {
     };
     if (uint32_t(lane) < len) nid = rv.vals[start + uint32_t(lane)];
     fetch(uint32_t(lane));
+    const bool finite = __builtin_amdgcn_readfirstlane(int(inf_colour)) == 0;
     uint32_t have = 0, pending = 0, at = 0;                      // (uniform)
     uint64_t picked = 0;                                         // lane p: who kept in the p-th look pending
     bool go = __ballot(Ts > 0.0f) != 0;
@@ -697,19 +705,29 @@ raster_fwd_px1_kernel(Table vt) {
         }
         wave_lds_sync();
         uint64_t bm[2] = {0, 0};
+        constexpr std::integral_constant<int, 1> one{};
+        constexpr std::integral_constant<int, 2> two{};
 #pragma unroll 1
         for (uint32_t b0 = 0; b0 < have && go; b0 += 64u) {
             const uint32_t top = min(have, b0 + 64u);
             uint64_t word = 0, bit = 1;
             Pair g0, g1;
-            load(g0, b0);
-            for (uint32_t e = b0; e < top && go; e += uint32_t(kListStep)) {
-                load(g1, e + 2u);
-                word |= blend_pair(g0, bit);
-                load(g0, e + uint32_t(kListStep));
-                word |= blend_pair(g1, bit << 2);
-                bit <<= kListStep;
-                go = __ballot(Ts > 0.0f) != 0;
+            if (__builtin_expect(finite, 1)) {
+                load(g0, b0);
+                for (uint32_t e = b0; e < top && go; e += uint32_t(kListStep)) {
+                    load(g1, e + 2u);
+                    word |= blend(two, g0, bit);
+                    load(g0, e + uint32_t(kListStep));
+                    word |= blend(two, g1, bit << 2);
+                    bit <<= kListStep;
+                    go = __ballot(Ts > 0.0f) != 0;
+                }
+            } else {                                             // (every entry looked after)
+                for (uint32_t e = b0; e < top && go; ++e, bit <<= 1) {
+                    load(g0, e);
+                    word |= blend(one, g0, bit);
+                    go = __ballot(Ts > 0.0f) != 0;
+                }
             }
             if (b0 == 0) bm[0] = word;
             else bm[1] = word;
