@@ -505,6 +505,8 @@ super_ranges(const uint32_t* __restrict__ row_total, const unsigned long long* _
     }
 }
 
+constexpr int kExpandStage = 1024;                         // entries staged at once
+
 // One block per chunk, one wavefront per tile row of its supertile: the chunk
 // is staged in LDS (a wavefront that loaded from memory between its stores
 // would wait for the stores too); of each 64 entries, those of the row are
@@ -523,13 +525,6 @@ super_ranges(const uint32_t* __restrict__ row_total, const unsigned long long* _
 // (886 M); whole lines take 240 and 920 us.  Measured and set aside: rings of
 // ids in LDS instead of the permutation (249-271, 906-925 us), a lane per tile
 // walking the entries (282, 985), every wavefront loading its own entries (289, 921).
-// A wavefront's store of one line from a scalar address.
-__device__ __forceinline__ void store_line(uint32_t* line, uint32_t lane4, uint32_t v) {
-    asm volatile("global_store_dword %0, %1, %2" : : "v"(lane4), "v"(v), "s"(line) : "memory");
-}
-
-constexpr int kExpandStage = 1024;                         // entries staged at once
-
 __global__ void __launch_bounds__(512)
 super_expand(const uint2* __restrict__ list, const uint4* __restrict__ desc,
              const uint32_t* __restrict__ nchunks, const uint32_t* __restrict__ tcnt,
@@ -558,7 +553,7 @@ super_expand(const uint2* __restrict__ list, const uint4* __restrict__ desc,
         off[k] = skip[k] = p & 63u;
         pend[k] = 0;
     }
-    const uint32_t nl4 = ~lane << 2, lane4 = lane << 2;
+    const uint32_t nl4 = ~lane << 2;
     uint2* kept = s_kept[r];
     uint32_t have = 0;                                         // entries in `kept` (< 64 between steps)
     auto append = [&](uint2 v) {                               // v.y: no column for no entry
@@ -577,13 +572,9 @@ super_expand(const uint2* __restrict__ list, const uint4* __restrict__ desc,
             pend[k] = y;
             off[k] += n[k];
             if (off[k] >= 64u) {                               // the line is complete
-                uint32_t* o = out + line[k];
-                if (skip[k] == 0u) {
-                    store_line(o, lane4, y);
-                } else {                                       // (begun by another chunk)
-                    if (lane >= skip[k]) o[lane] = y;
-                    skip[k] = 0u;
-                }
+                // (the places before this chunk's first are another's)
+                if (lane >= skip[k]) (out + line[k])[lane] = y;
+                skip[k] = 0u;
                 line[k] += 64u;
                 off[k] -= 64u;
                 pend[k] = x[k];
