@@ -68,8 +68,7 @@ uint64_t densify_workspace_bytes(int64_t n) {
     const uint64_t un = uint64_t(n);
     const uint64_t pairs = 4 * align_up(un * 4, 256);                 // keys and values, twice
     const uint64_t counts = align_up(radix_counts_elems(un) * 4, 256);
-    const uint64_t partials = align_up(scan_partials_elems(radix_counts_elems(un)) * 8, 256);
-    return 256 + pairs + counts + partials;
+    return 256 + pairs + counts;
 }
 
 hipError_t launch_densify(int64_t n, const float* pos, const float* col, const int32_t* count,
