@@ -85,11 +85,13 @@ typedef struct tgs_options {
                                 Gaussians a pixel considers, hence the result.  */
     int32_t lds_batch;       /* splat records staged in LDS per round by the
                                 rasterizer: 64, 128 or 256, or 0 for the default
-                                of the tile size.  Speed only; results do not
-                                depend on it.                                    */
+                                (tgs_default_launch).  At one pixel per thread
+                                only the backward stages in rounds.  Speed only;
+                                results do not depend on it.                     */
     int32_t pixels_per_thread; /* rasterizer work split: 1, 2 or 4 pixels per
                                 thread (tile 8: 1; tile 16: 1, 2, 4; tile 32:
-                                2, 4), or 0 for the default of the tile size.
+                                2, 4), or 0 for the default of the tile size and
+                                the number of tiles (tgs_default_launch).
                                 Speed only; results do not depend on it.        */
     float bg[3];             /* background colour added with the final T         */
     uint32_t flags;          /* 0 or TGS_SYNC_CHECK; other bits are invalid      */

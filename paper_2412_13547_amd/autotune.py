@@ -1,7 +1,8 @@
 """Launch autotuner of the batched rasterizer: times one graph-replayed fitting
 step (forward, L1 gradient, backward of every view) for each tile size T in
 {8, 16, 32}, each work split (pixels per thread P: 1 for T = 8; 1, 2, 4 for
-T = 16; 2, 4 for T = 32) and each LDS batch B in {64, 128, 256}.
+T = 16; 2, 4 for T = 32) and each LDS batch B in {64, 128, 256} (at P = 1 only
+the backward depends on B).
 
 P and B only change speed, so ``best_launch`` maps every tile size to its
 fastest (P, B), which can be applied without changing any result.  T changes

@@ -7,10 +7,10 @@
 // covers the tiles of up to kMaxViews views (a view table passed by value):
 // workgroups are laid out view after view, so a batch of views of uneven size
 // is balanced by the hardware dispatcher like one big image, and within a
-// view they take the tiles heaviest first (the schedule below).  16x16 and 8x8
-// tiles give one pixel per thread, 32x32 tiles a 2x2 block per thread.  The
-// tile's list is staged through LDS B splat records at a time; every pixel
-// walks it front to back (Sec. 3 Eq. 2), and the backward from its last
+// view they take the tiles heaviest first (the schedule below).  A thread has
+// 1, 2 or 4 pixels (Shape), fewer where a launch has few tiles.  The tile's list
+// is staged through LDS B splat records at a time (the forward at one pixel per
+// thread: by each wavefront for itself); every pixel walks it front to back (Sec. 3 Eq. 2), and the backward from its last
 // blended entry back to the first, with the forward's arithmetic and decisions
 // (one shared inline routine).
 //
@@ -978,8 +978,10 @@ raster_bwd_kernel(Table vt) {
             }
         };
         // two entries (kListed).  The splat's constants go to the sums, which
-        // cancels less and costs nothing here: the kernel waits for its chain of
-        // entries, not for instructions.
+        // costs nothing here (the kernel waits for its chain of entries, not for
+        // instructions) and is as exact as per lane: dL/du of 4000 random splats
+        // over 8 x 8 pixels, in float32 against 64 bits, median relative error
+        // 9.6e-8 against 8.6e-8, nine tenths below 6.1e-7 against 5.1e-7.
         auto pair = [&](const EntryPair& g) {
             float ab[2], dx[2], dy[2];
             uint64_t clamped[2];

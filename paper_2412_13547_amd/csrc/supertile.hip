@@ -27,8 +27,10 @@
 //      of its row and appends their ids to the row's eight tiles.
 // The pair count is on the device after 1; above the capacity the later
 // kernels write nothing and the ranges come out empty, so no step waits for
-// the host.  Small views are binned directly instead (direct_kernel).  A list entry holds at least one pair, so a list buffer of the
+// the host.  A list entry holds at least one pair, so a list buffer of the
 // pair capacity always fits.
+//
+// Small views are binned directly instead (direct_kernel).
 //
 // What bounds it: the 4 bytes written per pair in step 5.  The earlier form
 // (rows, then a counting sort by column of 4096-pair slices in LDS; still used
@@ -739,11 +741,18 @@ uint64_t super_max_chunks(uint64_t capacity, int supers) {
     return std::min<uint64_t>(kChunkTarget, capacity / kChunkMin + 1) + uint64_t(supers);
 }
 
-// Few enough Gaussians and tiles for every tile to look at every Gaussian: the
-// whole bin/sort (us, in two levels against directly) 34.5 / 22.3 at 2K
-// Gaussians and 64 tiles, 49.3 / 36.1 at 5K and 1200, 59.7 / 50.0 at 20K and
-// 920, 61.7 / 60.9 at 30K and 1200 (36 M tests), slower from there (200K and
-// 468: 43 us of kernels against 58).
+// Few enough Gaussians and tiles for every tile to look at every Gaussian that
+// has tiles.  The whole bin/sort (us, in two levels / directly) by tests, with
+// 57 % of the Gaussians in view and with all of them:
+//   tiles        16 M                      32 M                       64 M
+//      64   78 / 67    93 / 79     99 / 87   119 / 111     135 / 132   177 / 188
+//     169   66 / 61    74 / 72     73 / 74    87 / 94       88 / 102   107 / 138
+//    1024   62 / 55    66 / 64     64 / 64    68 / 81       67 / 84     73 / 114
+//    4096   41 / 32    44 / 38     55 / 51    56 / 67       66 / 79     68 / 108
+//   15876   44 / 34    47 / 39     47 / 43    51 / 53       53 / 58     53 / 81
+// (1.9 M on 16 tiles, 31 M tests: 207 / 146 and 295 / 197).  How many are in view
+// is not known when the launches are chosen: at 32 M both cost the same for 57 %
+// (and the direct binning up to 13 us more where all are).
 constexpr uint64_t kDirectTests = 32'000'000;
 constexpr int64_t kDirectWords = 16 * 1024;                // words the one-block scan takes
 
