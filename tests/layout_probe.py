@@ -41,6 +41,7 @@ int main() {
 }
 """
 PATHS = ("rows", "two levels", "direct")
+_TMP = tempfile.TemporaryDirectory(prefix="tgs_layout")      # (removed when the tests end)
 
 
 @functools.lru_cache(maxsize=1)
@@ -49,8 +50,7 @@ def _program() -> str:
     if cxx is None:
         pytest.skip("no host C++ compiler")
     api.lib()
-    tmp = tempfile.mkdtemp(prefix="tgs_layout")
-    src, exe = os.path.join(tmp, "layout.cpp"), os.path.join(tmp, "layout")
+    src, exe = os.path.join(_TMP.name, "layout.cpp"), os.path.join(_TMP.name, "layout")
     with open(src, "w") as f:
         f.write(PROGRAM)
     rocm = os.path.dirname(os.path.dirname(build.hipcc()))
